@@ -62,16 +62,17 @@ typedef enum {
  *   FMM_BF16X3 as FMM_BF16X2 with three pieces (hi + mid + lo) and the six products
  *              down to order 2^-16 (FP32-level error).  Needs an even nrhs.
  *
- * Kernels.  The streaming kernels run one workgroup per (group, polarisation,
- * right-hand side) and stream the factors from HBM once per right-hand side; they take
- * 64, 128, 256 or 512 threads by the mean item size, or as tuned (the environment
- * variable TUCKFMM_STREAM_THREADS, read at upload, fixes the default).  Untuned,
- * FMM_C128 and FMM_C64 run them for an odd nrhs and the matrix-core products (FP64
- * and FP32 MFMA) for an even nrhs; fmm_tucker_tune may choose differently for an nrhs
- * (it offers both paths at any nrhs for these two precisions).  FMM_C128 takes
- * the matrix cores at every nrhs when the layout's largest item does not fit the FP64
- * streaming kernels' LDS (they keep an item's x_g or core-stage vector and its r_beta
- * or angular intermediate there: about 10,000 complex128 values on 160 KB).  The
+ * Kernels.  The streaming kernels run one workgroup per (group, polarisation) and block of
+ * up to four right-hand sides and sweep the rows of its factors once: a pass reads them
+ * once for both stages.  They take 64, 128, 256 or 512 threads by the mean item size, or as
+ * tuned (the environment variable TUCKFMM_STREAM_THREADS, read at upload, fixes the
+ * default; rows too long for the size chosen take more).  Untuned, FMM_C128 and FMM_C64 run
+ * them for an odd nrhs and for 2 and 4, and the matrix-core products (FP64 and FP32 MFMA)
+ * for an even nrhs from 6; fmm_tucker_tune may choose differently for an nrhs (it offers
+ * both paths at any nrhs for these two precisions).  FMM_C128 takes the matrix cores at
+ * every nrhs when the layout's largest item does not fit the FP64 general streaming
+ * kernels' LDS (they keep an item's x_g or core-stage vector and its r_beta or angular
+ * intermediate there: about 10,000 complex128 values on 160 KB).  The
  * matrix-core path computes every contraction of
  * Section II.C as one grouped complex GEMM over all (group, polarisation) items for a
  * chunk of right-hand sides (factors read once per chunk); it keeps library-owned

@@ -78,24 +78,26 @@ int pack_elems(fmm_prec p) { return p == FMM_C128 ? 1 : 2; }
 bool prec_valid(int p) { return p >= FMM_C128 && p <= FMM_BF16X3; }
 bool prec_is_split(fmm_prec p) { return p == FMM_BF16X2 || p == FMM_BF16X3; }
 
-// Smallest even nrhs for which FMM_C64 and FMM_C128 take the matrix-core products
-// when untuned.  With two right-hand sides the matrix-core pass already beats the
-// streaming kernels, which read the factors once per right-hand side (30-lambda
-// sphere: FP32 2.70 against 3.83 ms, FP64 5.22 against 7.42 ms).
-constexpr int kMfmaMinRhs = 2;
+// Smallest even nrhs for which FMM_C64 and FMM_C128 take the matrix-core products when
+// untuned.  The streaming kernels read the factors once for both stages and up to four
+// right-hand sides: with two they take 137 to 253 us where the matrix cores take 281 to 426
+// (boxes of 0.5 to 2 lambda, 100 to 1000 groups, both precisions); with four the two are
+// within 30% of each other, with more the matrix cores win.
+constexpr int kMfmaMinRhs = 6;
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 bool aligned(const void* p, size_t a) { return reinterpret_cast<uintptr_t>(p) % a == 0; }
 
 // Device layout of one precision slot, computed identically for sizing and packing:
-// [header: items, work list, pass list][factors].
+// [header: items, work list][factors].
 struct ArenaPlan {
   size_t header_bytes = 0, factor_bytes = 0, total_bytes = 0, factor_bytes_paper = 0;
   std::vector<TuckItem> items;
   std::vector<TuckUnit> units;
   std::vector<TuckSplit> splits;
   int64_t part_stride = 0;
-  std::vector<int32_t> order, pass, zero_rows;
+  std::vector<TuckWork> work;      // the units, largest first
+  std::vector<int32_t> zero_rows;
   TuckMax mx{};
 };
 
@@ -112,11 +114,6 @@ constexpr int kSplitBelow = 128;
 constexpr double kSplitMin = 65536.0;
 constexpr double kSplitUnits = 512.0;
 constexpr int kSplitMinRows = 4;
-
-// LDS of one CU (gfx950), and the fewest wavefronts per CU with which the streaming
-// kernels stage the angular operands in LDS.
-constexpr size_t kCuLds = 160 * 1024;
-constexpr int kStageMinWaves = 8;
 
 double split_elems(const std::vector<TuckItem>& items) {
   if (const char* env = std::getenv("TUCKFMM_SPLIT_ELEMS")) {
@@ -168,7 +165,6 @@ fmm_status plan_arena(const fmm_tucker_s* h, fmm_prec prec, ArenaPlan* P) {
       if (!it.ident) {  // identity angular factors are not stored
         it.off_ut = (int64_t)(block((size_t)L.n_theta * it.rt) / es);
         it.off_up = (int64_t)(block((size_t)L.n_phi * it.rp) / es);
-        it.off_upt = (int64_t)(block((size_t)L.n_phi * it.rp) / es);
       }
       P->items[2 * g + a] = it;
       mx.nb = std::max(mx.nb, it.nb);
@@ -176,6 +172,8 @@ fmm_status plan_arena(const fmm_tucker_s* h, fmm_prec prec, ArenaPlan* P) {
       mx.rp = std::max(mx.rp, it.rp);
       mx.rb = std::max(mx.rb, it.rb);
       mx.q = std::max(mx.q, it.rt * it.rp);
+      mx.row = std::max(mx.row, it.ld_ub + it.ld_c);
+      mx.slices = std::max(mx.slices, (it.ld_ub / E + 63) / 64 + (it.ld_c / E + 63) / 64);
       if (!it.ident) mx.t3 = std::max(mx.t3, it.theta_first ? L.n_theta * it.rp : it.rt * L.n_phi);
       P->factor_bytes_paper +=
           it.ident ? es * ((size_t)it.rt * it.rp * it.rb + (size_t)it.nb * it.rb)   // W and U^beta
@@ -185,7 +183,6 @@ fmm_status plan_arena(const fmm_tucker_s* h, fmm_prec prec, ArenaPlan* P) {
   }
   mx.nt = L.n_theta;
   mx.np = L.n_phi;
-  mx.stage = 0;  // decided at upload, with the workgroup size
   P->mx = mx;
   // work units: whole items, or row blocks of the items above the split size
   const double split = split_elems(P->items);
@@ -223,21 +220,11 @@ fmm_status plan_arena(const fmm_tucker_s* h, fmm_prec prec, ArenaPlan* P) {
   P->part_stride = (agg_off + dis_off + 31) / 32 * 32;
   // work lists in longest-processing-time order
   const int n = (int)P->units.size();
-  P->order.resize(n);
-  std::iota(P->order.begin(), P->order.end(), 0);
-  std::stable_sort(P->order.begin(), P->order.end(), [&](int32_t a, int32_t b) { return ucost[a] > ucost[b]; });
-  // The pass list takes the aggregation and the disaggregation of the i-th largest
-  // unit in turn.  Workgroups go to the eight XCDs round-robin by index, so with the
-  // pair always in the same order the even XCDs would run only aggregation units and
-  // the odd ones only disaggregation units, which take longer on small boxes (the 0.5-
-  // lambda layout of the 20-lambda sphere: the two halves of the chip finished 623 and
-  // 900 us into the pass).  Every other group of four pairs is therefore swapped.
-  P->pass.resize((size_t)2 * n);
-  for (int i = 0; i < n; ++i) {
-    const int first = (i / 4) & 1;
-    P->pass[2 * i + first] = P->order[i];        // aggregation of the i-th largest unit
-    P->pass[2 * i + 1 - first] = ~P->order[i];   // and its disaggregation
-  }
+  std::vector<int32_t> order(n);
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return ucost[a] > ucost[b]; });
+  P->work.resize(n);
+  for (int i = 0; i < n; ++i) P->work[i] = TuckWork{P->items[P->units[order[i]].item], P->units[order[i]], 0};
   // box grid: the rows of the empty boxes, written zero by the aggregation
   if (!h->box.empty()) {
     std::vector<char> used((size_t)h->n_boxes, 0);
@@ -246,9 +233,8 @@ fmm_status plan_arena(const fmm_tucker_s* h, fmm_prec prec, ArenaPlan* P) {
       for (int64_t b = 0; b < h->n_boxes; ++b)
         if (!used[(size_t)b]) P->zero_rows.push_back((int32_t)(a * h->n_boxes + b));
   }
-  P->header_bytes = align_up(P->items.size() * sizeof(TuckItem) + P->units.size() * sizeof(TuckUnit) +
-                                 P->splits.size() * sizeof(TuckSplit) +
-                                 (P->order.size() + P->pass.size() + P->zero_rows.size()) * sizeof(int32_t),
+  P->header_bytes = align_up(P->items.size() * sizeof(TuckItem) + P->work.size() * sizeof(TuckWork) +
+                                 P->splits.size() * sizeof(TuckSplit) + P->zero_rows.size() * sizeof(int32_t),
                              256);
   P->factor_bytes = off;
   P->total_bytes = P->header_bytes + P->factor_bytes;
@@ -284,9 +270,6 @@ void pack_tensor(const Layout& L, const TensorFactors& tf, const TuckItem& it, S
   for (size_t i = 0; i < (size_t)nt * it.rt; ++i) put<S>(ut + 2 * i, tf.ut[i]);
   S* up = fac + 2 * it.off_up;
   for (size_t i = 0; i < (size_t)np * it.rp; ++i) put<S>(up + 2 * i, tf.up[i]);
-  S* upt = fac + 2 * it.off_upt;
-  for (int j = 0; j < np; ++j)
-    for (int c = 0; c < it.rp; ++c) put<S>(upt + 2 * ((size_t)c * np + j), tf.up[(size_t)j * it.rp + c]);
 }
 
 fmm_status check_vec(const void* p, size_t align, const char* name) {
@@ -336,7 +319,7 @@ bool mfma_allows(fmm_prec prec, int nrhs) { return !prec_is_split(prec) || nrhs 
 
 fmm_status route_of(const PrecSlot& s, fmm_prec prec, int nrhs, Route* r) {
   *r = Route{};
-  r->threads = s.threads;
+  r->threads = nrhs == 1 ? s.threads : s.threads_multi;
   for (const TuneChoice& t : s.tuned)
     if (t.nrhs == nrhs && t.path == 0 && t.threads) r->threads = t.threads;
   if (prec_is_split(prec)) {
@@ -632,18 +615,12 @@ extern "C" fmm_status fmm_tucker_upload(fmm_tucker_t h, fmm_prec prec, void* are
   char* p = img.data();
   std::memcpy(p, P.items.data(), P.items.size() * sizeof(TuckItem));
   p += P.items.size() * sizeof(TuckItem);
-  const size_t units_off = (size_t)(p - img.data());
-  std::memcpy(p, P.units.data(), P.units.size() * sizeof(TuckUnit));
-  p += P.units.size() * sizeof(TuckUnit);
+  const size_t work_off = (size_t)(p - img.data());
+  std::memcpy(p, P.work.data(), P.work.size() * sizeof(TuckWork));
+  p += P.work.size() * sizeof(TuckWork);
   const size_t splits_off = (size_t)(p - img.data());
   if (!P.splits.empty()) std::memcpy(p, P.splits.data(), P.splits.size() * sizeof(TuckSplit));
   p += P.splits.size() * sizeof(TuckSplit);
-  const size_t order_off = (size_t)(p - img.data());
-  std::memcpy(p, P.order.data(), P.order.size() * sizeof(int32_t));
-  p += P.order.size() * sizeof(int32_t);
-  const size_t pass_off = (size_t)(p - img.data());
-  std::memcpy(p, P.pass.data(), P.pass.size() * sizeof(int32_t));
-  p += P.pass.size() * sizeof(int32_t);
   const size_t zero_off = (size_t)(p - img.data());
   if (!P.zero_rows.empty()) std::memcpy(p, P.zero_rows.data(), P.zero_rows.size() * sizeof(int32_t));
   char* fac = img.data() + P.header_bytes;
@@ -678,26 +655,26 @@ extern "C" fmm_status fmm_tucker_upload(fmm_tucker_t h, fmm_prec prec, void* are
     double c = 0.0;
     for (const TuckUnit& u : P.units) c += item_cost(P.items[u.item]) * (u.b1 - u.b0) / P.items[u.item].rb;
     c /= std::max<size_t>(1, P.units.size());
-    // (measured on MI355X, FP32 pass.  Angular operands read from memory: mean 12k
-    // elements runs best at 64 threads, 50k at 128, 258k at 256, 1.7M at 512.  Staged
-    // in LDS, the shorter angular phases favour wider workgroups: 12k and 50k at 128,
-    // 258k at 512.)
-    const int t_plain = c >= 1.5e6 ? 512 : (c >= 1e5 ? 256 : (c >= 3e4 ? 128 : 64));
-    const int t_staged = c >= 1e5 ? 512 : (c >= 5e3 ? 128 : 64);
-    // Staging the angular operands (and G) in LDS shortens the angular phases but
-    // takes LDS from the resident workgroups: it pays while a CU still holds
-    // kStageMinWaves wavefronts (FP64 at 1-lambda boxes, 4 wavefronts staged, ran
-    // 1.24 ms unstaged and 1.59 ms staged; every layout with 8 or more gained).
-    TuckMax ms = P.mx;
-    ms.stage = 1;
-    const size_t staged = prec == FMM_C128 ? tucker_lds_bytes<double>(ms) : tucker_lds_bytes<float>(ms);
-    const int waves = staged > kCuLds ? 0 : (int)(kCuLds / staged) * (t_staged / 64);
-    P.mx.stage = staged <= (size_t)lds_lim && waves >= kStageMinWaves ? 1 : 0;
-    if (const char* env = std::getenv("TUCKFMM_STAGE_ANGULAR")) P.mx.stage = P.mx.stage && std::atoi(env) != 0;
-    sl.threads = P.mx.stage ? t_staged : t_plain;
+    // (measured on MI355X, 1 right-hand side, complex64 pass: mean 15k elements takes 133 us
+    // with 256 threads, 149 with 128 and 204 with 512; 140k takes 118 with 512 and 125 with
+    // 256; 259k 229 with 512 and 321 with 256.  Where the angular operands don't fit LDS, the
+    // old line stands.)
+    const int t_plain = c >= 1e5 ? 512 : (c >= 3e4 ? 256 : 128);
+    const int t_staged = c >= 3e4 ? 512 : (c >= 4e3 ? 256 : 128);
+    P.mx.lds = lds_lim;
+    P.mx.stage = 1;
+    if (const char* env = std::getenv("TUCKFMM_STAGE_ANGULAR")) P.mx.stage = std::atoi(env) != 0;
+    StreamFit f{};
+    const bool fits = prec == FMM_C128 ? stream_fits<double>(P.mx, t_staged, 1, true, &f)
+                                       : stream_fits<float>(P.mx, t_staged, 1, true, &f);
+    sl.threads = fits && f.staged ? t_staged : t_plain;
+    // several right-hand sides leave fewer wavefronts per CU: smaller workgroups keep more
+    // units in flight (140k elements, 3 and 5 right-hand sides, complex64: 230 and 347 us
+    // with 128 threads, 252 and 426 with 512; complex128: 484 and 740 against 444 and 693)
+    sl.threads_multi = prec != FMM_C128 && c < 2e5 ? 128 : sl.threads;
     if (const char* env = std::getenv("TUCKFMM_STREAM_THREADS")) {
       const int v = std::atoi(env);
-      if (v == 64 || v == 128 || v == 256 || v == 512) sl.threads = v;
+      if (v == 64 || v == 128 || v == 256 || v == 512) sl.threads = sl.threads_multi = v;
     }
   }
   sl.streams = (prec == FMM_C128 ? tucker_lds_bytes<double>(P.mx) : tucker_lds_bytes<float>(P.mx)) <=
@@ -708,11 +685,9 @@ extern "C" fmm_status fmm_tucker_upload(fmm_tucker_t h, fmm_prec prec, void* are
   sl.device = dev;
   TuckPlan& pl = sl.plan;
   pl.items = reinterpret_cast<const TuckItem*>(sl.arena);
-  pl.order = reinterpret_cast<const int32_t*>(sl.arena + order_off);
-  pl.pass_list = reinterpret_cast<const int32_t*>(sl.arena + pass_off);
   pl.zero_rows = P.zero_rows.empty() ? nullptr : reinterpret_cast<const int32_t*>(sl.arena + zero_off);
   pl.n_zero_rows = (int)P.zero_rows.size();
-  pl.units = reinterpret_cast<const TuckUnit*>(sl.arena + units_off);
+  pl.work = reinterpret_cast<const TuckWork*>(sl.arena + work_off);
   pl.splits = P.splits.empty() ? nullptr : reinterpret_cast<const TuckSplit*>(sl.arena + splits_off);
   pl.n_units = (int)P.units.size();
   pl.n_splits = (int)P.splits.size();

@@ -11,7 +11,6 @@ namespace tuckfmm {
 //   core : [r_beta][ld_c], column q = theta' * r_phi + phi'
 //   ut   : U^theta [n_theta][r_theta]
 //   up   : U^phi [n_phi][r_phi]
-//   upt  : U^phi transposed, [r_phi][n_phi]
 // Row padding elements are zero.  An item with identity angular factors (the
 // truncated-SVD method: r_theta = n_theta, r_phi = n_phi, U^theta = U^phi = I) has
 // ident = 1, stores no angular factors, and its core is W (column q = direction).
@@ -20,7 +19,6 @@ struct alignas(16) TuckItem {
   int64_t off_core;
   int64_t off_ut;
   int64_t off_up;
-  int64_t off_upt;
   int64_t row0;      // first basis row of the group
   int32_t nb, rt, rp, rb;
   int32_t ld_ub, ld_c;
@@ -28,7 +26,7 @@ struct alignas(16) TuckItem {
   int32_t theta_first;  // 1: contract U^theta before U^phi in the angular stages
   int32_t ident;        // 1: identity angular factors (no angular products)
   int32_t frow;         // row of the item's fibre in F and G: 2 group + alpha, or alpha K + box on a box grid
-  int32_t pad2;
+  int32_t pad2[3];
 };
 static_assert(sizeof(TuckItem) == 96, "TuckItem layout");
 
@@ -42,6 +40,15 @@ struct TuckUnit {
   int32_t pad;
 };
 static_assert(sizeof(TuckUnit) == 24, "TuckUnit layout");
+
+// Entry of the streaming work list, largest unit first: the unit with its item's fields, so
+// that a workgroup reads one record and not a chain of them.
+struct alignas(16) TuckWork {
+  TuckItem it;
+  TuckUnit u;
+  int64_t pad;
+};
+static_assert(sizeof(TuckWork) == 128, "TuckWork layout");
 
 // A split item: its n_parts partial blocks, per right-hand side at
 //   agg: part + r part_stride + agg_off + s q_pad   (q_pad complex values each)
@@ -59,25 +66,23 @@ struct TuckMax {
   int32_t nb, rt, rp, rb, q;
   int32_t t3;      // max of n_theta*r_phi or r_theta*n_phi intermediate
   int32_t nt, np;  // the direction grid n_theta x n_phi
-  int32_t stage;   // 1: the angular products read their factors (and G) from LDS
+  int32_t row;     // complex values of a row of U^beta^T and the core together, with padding
+  int32_t slices;  // slices of 64 packs of such a row, each operand's last one rounded up
+  int32_t lds;     // LDS a workgroup may take (bytes)
+  int32_t stage;   // 1: the angular products may read their factors (and G) from LDS
 };
 
 // Device pointers and sizes of one uploaded precision.
-//   units     : the work units (whole items and row blocks of split items)
-//   order     : the units, largest first
-//   pass_list : 2 n_units entries of a whole pass, largest first; entry e >= 0 is the
-//               aggregation of unit e, e < 0 the disaggregation of unit ~e
+//   work      : the work units (whole items and row blocks of split items), largest first
 //   splits    : the split items, summed by the finishing kernel
 //   zero_rows : on a box grid, the rows alpha K + box of the empty boxes, which the
 //               aggregation writes zero
 struct TuckPlan {
   const void* factors = nullptr;
   const TuckItem* items = nullptr;
-  const int32_t* order = nullptr;
-  const int32_t* pass_list = nullptr;
   const int32_t* zero_rows = nullptr;  // rows of F on empty boxes (box grid only)
   int n_zero_rows = 0;
-  const TuckUnit* units = nullptr;
+  const TuckWork* work = nullptr;
   const TuckSplit* splits = nullptr;
   int n_units = 0, n_splits = 0;
   int64_t part_stride = 0;  // partial-sum elements per right-hand side

@@ -89,6 +89,7 @@ struct PrecSlot {
   TuckPlan plan;          // device pointers into the arena
   std::vector<TuckItem> items;      // host copy of the item table
   int threads = 512;                // default workgroup size of the streaming kernels
+  int threads_multi = 512;          // the same with several right-hand sides
   bool streams = true;              // the streaming kernels' LDS fits the largest item
   std::list<MrhsPlan> mrhs;         // built on first use per (nrhs, knobs); stable addresses
   std::vector<TuneChoice> tuned;

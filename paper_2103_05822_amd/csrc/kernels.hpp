@@ -17,9 +17,24 @@ hipError_t launch_tucker_disagg(const TuckPlan& pl, int threads, int n_theta, in
 template <typename T>
 hipError_t launch_tucker_pass(const TuckPlan& pl, int threads, int n_theta, int n_phi, int nrhs, const void* x,
                               void* F, const void* G, void* V, hipStream_t s);
-// Largest dynamic LDS request of the Tucker kernels.
+// LDS of the general Tucker kernels, which bounds the layouts that the streaming path
+// takes.
 template <typename T>
 size_t tucker_lds_bytes(const TuckMax& mx);
+
+// LDS of one CU (gfx950), and the fewest wavefronts per CU with which the streaming
+// kernels stage the angular operands in LDS.
+constexpr size_t kCuLds = 160 * 1024;
+constexpr int kStageMinWaves = 8;
+// The row-streaming kernel that a layout takes: workgroup size, slices per wavefront,
+// right-hand sides per read of the factors, staging, LDS bytes.  `dis`: with the
+// disaggregation.
+struct StreamFit {
+  int threads, jmax, rb, staged;
+  size_t lds;
+};
+template <typename T>
+bool stream_fits(const TuckMax& mx, int threads, int nrhs, bool dis, StreamFit* out);
 
 // Grouped complex GEMM of the multi-RHS path (variant 0: FP32 MFMA, 1: BF16 two-piece
 // split, 2: BF16 three-piece split, all on complex64 data with FP32 accumulation;

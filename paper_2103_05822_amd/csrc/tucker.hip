@@ -1,31 +1,27 @@
-// Tucker-format aggregation and disaggregation (Section II.C, Figs. 2(b) and 3(b)).
+// Tucker-format aggregation and disaggregation (Section II.C, Figs. 2(b) and 3(b)) for one
+// to a few right-hand sides.
 //
-// One workgroup of NT = 64, 128, 256 or 512 threads (NT / 64 wavefronts) per
-// (group, polarisation) work item, NT chosen from the mean item size.  The two large
-// operands of an item -- U^beta and the core -- are streamed once from HBM with
-// 16-byte coalesced loads; every intermediate stays in LDS.  Work lists are sorted by
-// decreasing cost, so the hardware dispatcher hands out the largest items first
-// (longest-processing-time order).  The pass kernel runs the aggregation and
-// disaggregation items of all groups in one launch.  In layouts of few items, large
-// items run as blocks of their r_beta rows (work units) whose partial sums a
-// finishing kernel adds in block order.
+// One workgroup of NT = 64, 128, 256 or 512 threads per (group, polarisation) work item and
+// block of right-hand sides, NT chosen from the mean item size.  Work lists are sorted by
+// decreasing cost (longest-processing-time order).  In layouts of few items, large items
+// run as blocks of their r_beta rows (work units) whose partial sums a finishing kernel adds
+// in block order.  Per item (g, alpha), the angular order chosen on the host:
+//   S[a,c] = sum U^theta[i][a] U^phi[j][c] conj(G[i,j])    angular phase, matrix cores
+//   for every row b of U^beta^T and the core:
+//     y[b] = sum_n U^beta[n][b] x[n],   t[q] += core[b][q] y[b]
+//     s[b] = sum_q core[b][q] S[q],     v[n] += U^beta[n][b] s[b]
+//   F[i,j] = sum U^theta[i][a] U^phi[j][c] t[a, c]         angular phase, matrix cores
+//   V[n]  += conj(v[n])   atomically onto a zeroed V: each entry receives exactly two
+//            additions onto zero, one per polarisation, which commute exactly, so the
+//            result does not depend on which polarisation finishes first.
+// The sweep over the rows reads each factor once for both stages (the row-streaming kernels
+// below).  Rows too long for its registers run on the general kernels, one per stage, which
+// keep every vector in LDS.
 //
-// Aggregation of item (g, alpha), contraction order chosen per item on the host:
-//   y[b]    = sum_n U^beta[n][b] x[n]          row-dot of each U^beta^T row (one
-//                                              wavefront per row, lane-strided
-//                                              16-byte loads, butterfly reduction)
-//   t[q]    = sum_b core[b][q] y[b]            column axpy over the core rows
-//                                              (one thread per column pack)
-//   F[i,j]  = sum U^theta[i][a] U^phi[j][c] t[a, c]   two small LDS products
-// Disaggregation of item (g, alpha), the polarisations summed as in eq. (5):
-//   S[a,c]  = sum U^theta[i][a] U^phi[j][c] conj(G[i,j])   small LDS products
-//   s[b]    = sum_q core[b][q] S[q]            row-dot of each core row
-//   V[n]   += conj(sum_b U^beta[n][b] s[b])    column axpy over U^beta^T, added
-//                                              atomically onto a zeroed V: each
-//                                              entry receives exactly two additions
-//                                              onto zero, which commute exactly, so
-//                                              the result does not depend on which
-//                                              polarisation finishes first.
+// One-right-hand-side pass on an MI355X, before (one read of the factors per stage, angular
+// products on the vector units) and now: 4000 items of mean 15k elements, complex64, 231 and
+// 135 us (510 MB: 3.8 TB/s); 512 items of mean 259k 398 and 230 us (1.2 GB: 5.2 TB/s); both
+// stages alone, complex128, 800 items of mean 58k 472 and 310 us (1.6 GB: 5.2 TB/s).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -35,21 +31,22 @@
 
 namespace tuckfmm {
 
+// This file is compiled twice, for each of the two element types (see tucker_f64.hip).
+#ifdef TUCKFMM_STREAM_F64
+using Real = double;
+#else
+using Real = float;
+#endif
+
 namespace {
 
-// Workgroup size NT (64, 128, 256 or 512 threads, NT / 64 wavefronts) is a template
-// parameter of every phase: one workgroup per item.
+// The general kernels' workgroup size.
+constexpr int kGenThreads = 512;
 constexpr int kColPacks = 2;  // column packs per thread per chunk in the axpy stages
-// K values per step of the small angular products in the 64- and 128-thread kernels
-// (small items): all of a step's operands are loaded before its multiply-adds.
-constexpr int kSmallKUnroll = 4;
-
-// U^beta^T and the core are read once per pass: non-temporal loads keep these
-// streams from displacing x, G, V and the work tables in the caches.  Measured on
-// MI355X they pay off for large items (5-7% on layouts with boxes of 2 lambda and
-// more) and cost about 4% on small ones (0.5 lambda boxes), so only the 256- and
-// 512-thread instantiations, which the workgroup-size rule picks for large items,
-// use them.
+// U^beta^T and the core are read once per call: the 256- and 512-thread kernels, which large
+// items take, load them non-temporally, so that these streams don't displace x, G, V and
+// the work tables in the caches (5-7% on boxes of 2 wavelengths and more; on small items it
+// cost 4%).
 template <typename P>
 struct NtVec;
 template <>
@@ -69,14 +66,13 @@ __device__ __forceinline__ P ldnt(const P* p) {
   return o;
 }
 
-// LDS regions (complex elements).
+// LDS regions of the general kernels (complex elements).
 // Aggregation:    r1 = x (n_beta), later t (r_theta r_phi);  r2 = y (r_beta), later
-//                 the angular intermediate; with staging, sa = U^theta and U^phi^T.
-// Disaggregation: s1 = angular intermediate, S (r_theta r_phi), s (r_beta); with
-//                 staging, sd = conj(G) of the item and one angular factor at a time.
+//                 the angular intermediate.
+// Disaggregation: s1 = angular intermediate, S (r_theta r_phi), s (r_beta).
 template <typename T>
 struct Lds {
-  int r1, r2, s1, s2, s3, sa, sd;
+  int r1, r2, s1, s2, s3;
   __host__ __device__ explicit Lds(const TuckMax& mx) {
     constexpr int E = Tr<T>::E;
     r1 = round_up(max(round_up(mx.nb, E), round_up(mx.q, E)), 2);
@@ -84,11 +80,9 @@ struct Lds {
     s1 = round_up(mx.t3, 2);
     s2 = round_up(round_up(mx.q, E), 2);
     s3 = round_up(mx.rb, 2);
-    sa = mx.stage ? round_up(mx.nt * mx.rt, 2) + round_up(mx.np * mx.rp, 2) : 0;
-    sd = mx.stage ? round_up(mx.nt * mx.np, 2) + round_up(max(mx.nt * mx.rt, mx.np * mx.rp), 2) : 0;
   }
-  __host__ __device__ size_t agg_bytes() const { return size_t(r1 + r2 + sa) * sizeof(typename Tr<T>::c); }
-  __host__ __device__ size_t dis_bytes() const { return size_t(s1 + s2 + s3 + sd) * sizeof(typename Tr<T>::c); }
+  __host__ __device__ size_t agg_bytes() const { return size_t(r1 + r2) * sizeof(typename Tr<T>::c); }
+  __host__ __device__ size_t dis_bytes() const { return size_t(s1 + s2 + s3) * sizeof(typename Tr<T>::c); }
   __host__ __device__ size_t bytes() const { return agg_bytes() > dis_bytes() ? agg_bytes() : dis_bytes(); }
 };
 
@@ -294,53 +288,69 @@ __device__ __forceinline__ void block_colaxpy(const typename Tr<T>::c* rows, int
   }
 }
 
-// out(m, n) = sum_k a(m, k) * b(k, n) for m < M, n < N: a small complex product
-// computed by the whole workgroup in tiles of four rows per thread, n across
-// threads, so that a(m, k) is a broadcast load shared by the four accumulators and
-// b(k, n) a coalesced load.
-template <typename C, int NT, class FA, class FB, class FO>
+// FP32 and FP64 matrix instructions of 16 x 16 x 4: lane l feeds row (column) l % 16 and
+// k = l / 16 of A (B); register i of lane l holds column l % 16 of row 4 (l / 16) + i
+// (FP32) or 4 i + l / 16 (FP64).
+template <typename T>
+struct Mfma;
+template <>
+struct Mfma<float> {
+  typedef float acc __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ acc mul(float a, float b, acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int i, int g) { return 4 * g + i; }
+};
+template <>
+struct Mfma<double> {
+  typedef double acc __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ acc mul(double a, double b, acc c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int i, int g) { return 4 * i + g; }
+};
+
+// out(m, n) = sum_k a(m, k) * b(k, n) for m < M, n < N: a small complex product of the
+// angular phases, computed by the whole workgroup on the matrix cores in tiles of
+// 16 x 16 values, tiles over wavefronts.  Four real products make a complex one; a step
+// of 4 K values reads one value of each operand per lane.  (On the vector units, with
+// four rows per thread, the products read five LDS values per four complex multiply-adds
+// and were bound by that.)
+template <typename T, int NT, class FA, class FB, class FO>
 __device__ __forceinline__ void tile_product(int M, int N, int K, FA a, FB b, FO out, int tid) {
-  const int tasks = (M + 3) / 4 * N;
-  for (int task = tid; task < tasks; task += NT) {
-    const int m0 = task / N * 4, n = task - task / N * N;
-    C acc[4];
+  using C = typename Tr<T>::c;
+  using Acc = typename Mfma<T>::acc;
+  constexpr int KU = 4;  // steps whose operands are loaded before their products
+  const int lane = tid & 63, li = lane & 15, g = lane >> 4;
+  const int mt = (M + 15) >> 4, tiles = mt * ((N + 15) >> 4);
+  for (int t = __builtin_amdgcn_readfirstlane(tid >> 6); t < tiles; t += NT / 64) {
+    const int n0 = t / mt * 16, m0 = (t - t / mt * mt) * 16;
+    const int m = min(m0 + li, M - 1), n = min(n0 + li, N - 1);  // (rows past the end are not stored)
+    Acc re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+    for (int k0 = 0; k0 < K; k0 += 4 * KU) {
+      C av[KU], bv[KU];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) acc[u] = czero<C>();
-    if (m0 + 3 < M) {
-      // KU values of K per step, all operands loaded before the multiply-adds: with
-      // operands in global memory each step costs about one memory latency
-      constexpr int KU = NT <= 128 ? kSmallKUnroll : 2;
-      int k = 0;
-      for (; k + KU - 1 < K; k += KU) {
-        C bv[KU], av[4][KU];
-#pragma unroll
-        for (int j = 0; j < KU; ++j) bv[j] = b(k + j, n);
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-          for (int j = 0; j < KU; ++j) av[u][j] = a(m0 + u, k + j);
-#pragma unroll
-        for (int j = 0; j < KU; ++j)
-#pragma unroll
-          for (int u = 0; u < 4; ++u) cfma(acc[u], av[u][j], bv[j]);
-      }
-      for (; k < K; ++k) {
-        const C b0 = b(k, n);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) cfma(acc[u], a(m0 + u, k), b0);
+      for (int j = 0; j < KU; ++j) {
+        const int k = k0 + 4 * j + g, kc = min(k, K - 1);
+        av[j] = a(m, kc);
+        bv[j] = b(kc, n);
+        if (k >= K) av[j] = bv[j] = czero<C>();
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) out(m0 + u, n, acc[u]);
-    } else {
-      for (int k = 0; k < K; ++k) {
-        const C b0 = b(k, n);
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (m0 + u < M) cfma(acc[u], a(m0 + u, k), b0);
+      for (int j = 0; j < KU; ++j) {
+        if (k0 + 4 * j >= K) break;
+        re = Mfma<T>::mul(av[j].x, bv[j].x, re);
+        im = Mfma<T>::mul(av[j].x, bv[j].y, im);
+        re = Mfma<T>::mul(-av[j].y, bv[j].y, re);
+        im = Mfma<T>::mul(av[j].y, bv[j].x, im);
       }
+    }
+    if (n0 + li < N) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (m0 + u < M) out(m0 + u, n, acc[u]);
+      for (int i = 0; i < 4; ++i) {
+        const int row = m0 + Mfma<T>::row(i, g);
+        if (row < M) out(row, n0 + li, C{re[i], im[i]});
+      }
     }
   }
 }
@@ -399,148 +409,175 @@ __device__ __forceinline__ void agg_stream(const typename Tr<T>::c* __restrict__
   }
 }
 
-// The two angular products of the aggregation, F = U^theta t U^phi^T, with the
-// factors at `ut` [n_theta][r_theta] and `upt` [r_phi][n_phi] (global memory or LDS).
-template <typename C, int NT>
-__device__ __forceinline__ void agg_angular_products(const TuckItem& it, int n_theta, int n_phi, int nrhs,
-                                                     const C* ts, C* t3, const C* ut, const C* upt, C* Fo,
-                                                     int tid) {
-  const int rt = it.rt, rp = it.rp;
-  if (it.theta_first) {
-    // t3[i][c] = sum_a U^theta[i][a] t[a][c]           (n_theta x r_phi)
-    tile_product<C, NT>(
-        n_theta, rp, rt, [&](int i, int a) { return ut[i * rt + a]; }, [&](int a, int c) { return ts[a * rp + c]; },
-        [&](int i, int c, C v) { t3[i * rp + c] = v; }, tid);
-    __syncthreads();
-    // F[i][j] = sum_c t3[i][c] U^phi[j][c]
-    tile_product<C, NT>(
-        n_theta, n_phi, rp, [&](int i, int c) { return t3[i * rp + c]; },
-        [&](int c, int j) { return upt[c * n_phi + j]; },
-        [&](int i, int j, C v) { Fo[(int64_t)(i * n_phi + j) * nrhs] = v; }, tid);
-  } else {
-    // t3[a][j] = sum_c t[a][c] U^phi[j][c]             (r_theta x n_phi)
-    tile_product<C, NT>(
-        rt, n_phi, rp, [&](int a, int c) { return ts[a * rp + c]; }, [&](int c, int j) { return upt[c * n_phi + j]; },
-        [&](int a, int j, C v) { t3[a * n_phi + j] = v; }, tid);
-    __syncthreads();
-    // F[i][j] = sum_a U^theta[i][a] t3[a][j]
-    tile_product<C, NT>(
-        n_theta, n_phi, rt, [&](int i, int a) { return ut[i * rt + a]; },
-        [&](int a, int j) { return t3[a * n_phi + j]; },
-        [&](int i, int j, C v) { Fo[(int64_t)(i * n_phi + j) * nrhs] = v; }, tid);
+// The angular factors where the angular phases read them: U^theta [n_theta][r_theta] and
+// U^phi [n_phi][r_phi], in global memory, or staged in LDS with odd row strides (which
+// spread the matrix instructions' operand reads over the banks).  The address space is in
+// the type, so that neither becomes a flat access.
+template <typename C>
+struct GlobalAngular {
+  const C* __restrict__ ut;
+  const C* __restrict__ up;
+  int ldt, ldp;
+  __device__ __forceinline__ C t(int i, int a) const { return ut[i * ldt + a]; }
+  __device__ __forceinline__ C p(int j, int c) const { return up[j * ldp + c]; }
+};
+template <typename C>
+struct LdsAngular {
+  typedef const C __attribute__((address_space(3))) * Ptr;
+  Ptr ut, up;
+  int ldt, ldp;
+  __device__ __forceinline__ C t(int i, int a) const { return lds_value(ut + i * ldt + a); }
+  __device__ __forceinline__ C p(int j, int c) const { return lds_value(up + j * ldp + c); }
+  static __device__ __forceinline__ C lds_value(Ptr q) {
+    typedef decltype(C{}.x) R2 __attribute__((ext_vector_type(2)));
+    const R2 v = *(const R2 __attribute__((address_space(3))) *)q;
+    return C{v.x, v.y};
   }
+};
+template <typename T>
+__device__ __forceinline__ GlobalAngular<typename Tr<T>::c> global_angular(const typename Tr<T>::c* fac,
+                                                                            const TuckItem& it) {
+  return {fac + it.off_ut, fac + it.off_up, it.rt, it.rp};
+}
+// Staged by stage_in at `us` (an LDS address).
+template <typename T>
+__device__ __forceinline__ LdsAngular<typename Tr<T>::c> staged_angular(const typename Tr<T>::c* us,
+                                                                         const TuckItem& it, int n_theta) {
+  using P = typename LdsAngular<typename Tr<T>::c>::Ptr;
+  return {(P)us, (P)(us + round_up(n_theta * (it.rt | 1), 2)), it.rt | 1, it.rp | 1};
 }
 
-// Angular phase: F = U^theta t U^phi^T from t in LDS (`ts`); the intermediate uses
-// LDS region r2.
-template <typename T, int NT>
-__device__ __forceinline__ void agg_angular(const typename Tr<T>::c* __restrict__ fac, const TuckItem& it,
-                                            const Lds<T>& L, unsigned char* smem, const typename Tr<T>::c* ts,
-                                            int n_theta, int n_phi, int nrhs, int r,
+// Angular phase of the aggregation: F = U^theta t U^phi^T from t in LDS (`ts`), with the
+// intermediate at `t3`.
+template <typename T, int NT, class FA>
+__device__ __forceinline__ void agg_angular(const TuckItem& it, const FA& f, typename Tr<T>::c* t3,
+                                            const typename Tr<T>::c* ts, int n_theta, int n_phi, int nrhs, int r,
                                             typename Tr<T>::c* __restrict__ F) {
   using C = typename Tr<T>::c;
-  C* t3 = reinterpret_cast<C*>(smem) + L.r1;
   const int tid = threadIdx.x;
   const int rt = it.rt, rp = it.rp;
-  const C* ut = fac + it.off_ut;    // [n_theta][rt]
-  const C* upt = fac + it.off_upt;  // [rp][n_phi]
   const int ndir = n_theta * n_phi;
   C* Fo = F + ((int64_t)it.frow * ndir) * nrhs + r;
   if (it.ident) {  // truncated-SVD item: t already holds the directions
     for (int i = tid; i < ndir; i += NT) Fo[(int64_t)i * nrhs] = ts[i];
     return;
   }
-  if (L.sa) {
-    // the factors into LDS (one load latency for both) after the r1 and r2 regions:
-    // the products then take one LDS access per K step instead of a memory latency
-    C* s_ut = reinterpret_cast<C*>(smem) + L.r1 + L.r2;
-    C* s_upt = s_ut + round_up(n_theta * rt, 2);
-    for (int q = tid; q < n_theta * rt; q += NT) s_ut[q] = ut[q];
-    for (int q = tid; q < rp * n_phi; q += NT) s_upt[q] = upt[q];
+  if (it.theta_first) {
+    // t3[i][c] = sum_a U^theta[i][a] t[a][c]           (n_theta x r_phi)
+    tile_product<T, NT>(
+        n_theta, rp, rt, [&](int i, int a) { return f.t(i, a); },
+        [&](int a, int c) { return ts[a * rp + c]; }, [&](int i, int c, C v) { t3[i * rp + c] = v; }, tid);
     __syncthreads();
-    agg_angular_products<C, NT>(it, n_theta, n_phi, nrhs, ts, t3, s_ut, s_upt, Fo, tid);
+    // F[i][j] = sum_c t3[i][c] U^phi[j][c]
+    tile_product<T, NT>(
+        n_theta, n_phi, rp, [&](int i, int c) { return t3[i * rp + c]; },
+        [&](int c, int j) { return f.p(j, c); },
+        [&](int i, int j, C v) { Fo[(int64_t)(i * n_phi + j) * nrhs] = v; }, tid);
   } else {
-    agg_angular_products<C, NT>(it, n_theta, n_phi, nrhs, ts, t3, ut, upt, Fo, tid);
+    // t3[a][j] = sum_c t[a][c] U^phi[j][c]             (r_theta x n_phi)
+    tile_product<T, NT>(
+        rt, n_phi, rp, [&](int a, int c) { return ts[a * rp + c]; },
+        [&](int c, int j) { return f.p(j, c); }, [&](int a, int j, C v) { t3[a * n_phi + j] = v; }, tid);
+    __syncthreads();
+    // F[i][j] = sum_a U^theta[i][a] t3[a][j]
+    tile_product<T, NT>(
+        n_theta, n_phi, rt, [&](int i, int a) { return f.t(i, a); },
+        [&](int a, int j) { return t3[a * n_phi + j]; },
+        [&](int i, int j, C v) { Fo[(int64_t)(i * n_phi + j) * nrhs] = v; }, tid);
   }
 }
 
 // --------------------------------------------------------------- disaggregation
 
-// Angular phase: S = U^theta^T conj(G) U^phi, written with its pack padding to
-// `S2` in LDS.  With zero_v the item also clears its rows of V.
-template <typename T, int NT>
-__device__ __forceinline__ void dis_angular(const typename Tr<T>::c* __restrict__ fac, const TuckItem& it,
-                                            const Lds<T>& L, unsigned char* smem, int n_theta, int n_phi,
-                                            int nrhs, int r, const typename Tr<T>::c* __restrict__ Gin,
-                                            typename Tr<T>::c* S2, bool zero_v, typename Tr<T>::c* __restrict__ V) {
+// Angular phase of the disaggregation: S = U^theta^T conj(G) U^phi, written with its pack
+// padding to `S2` in LDS, with the intermediate at `s1`.  `gc(q)`: conj(G) of direction q.
+template <typename T, int NT, class FA, class FG>
+__device__ __forceinline__ void dis_angular(const TuckItem& it, const FA& f, typename Tr<T>::c* s1, int n_theta,
+                                            int n_phi, FG gc, typename Tr<T>::c* S2) {
   using C = typename Tr<T>::c;
-  constexpr int E = Tr<T>::E;
-  C* s1 = reinterpret_cast<C*>(smem);
   const int tid = threadIdx.x;
-  const int ndir = n_theta * n_phi;
   const int rt = it.rt, rp = it.rp, Q = rt * rp;
-  const C* ut = fac + it.off_ut;  // [n_theta][rt]
-  const C* up = fac + it.off_up;  // [n_phi][rp]
-  const C* Gi = Gin + ((int64_t)it.frow * ndir) * nrhs + r;
-  if (zero_v)
-    for (int n = tid; n < it.nb; n += NT) V[(it.row0 + n) * nrhs + r] = czero<C>();
   // the angular order mirrors the aggregation choice
   if (it.ident) {  // truncated-SVD item: S2 is conj(G) itself
-    for (int q = tid; q < Q; q += NT) S2[q] = conjc(Gi[(int64_t)q * nrhs]);
-  } else if (L.sd) {
-    // conj(G) and the first product's factor into LDS after the s regions (one load
-    // latency), then the second product's factor in their place
-    C* gs = reinterpret_cast<C*>(smem) + L.s1 + L.s2 + L.s3;
-    C* fs = gs + round_up(ndir, 2);
-    for (int q = tid; q < ndir; q += NT) gs[q] = conjc(Gi[(int64_t)q * nrhs]);
-    if (!it.theta_first) {
-      for (int q = tid; q < n_theta * rt; q += NT) fs[q] = ut[q];
-      __syncthreads();
-      tile_product<C, NT>(
-          rt, n_phi, n_theta, [&](int a, int i) { return fs[i * rt + a]; },
-          [&](int i, int j) { return gs[i * n_phi + j]; }, [&](int a, int j, C v) { s1[a * n_phi + j] = v; }, tid);
-      __syncthreads();
-      for (int q = tid; q < n_phi * rp; q += NT) gs[q] = up[q];
-      __syncthreads();
-      tile_product<C, NT>(
-          rt, rp, n_phi, [&](int a, int j) { return s1[a * n_phi + j]; }, [&](int j, int c) { return gs[j * rp + c]; },
-          [&](int a, int c, C v) { S2[a * rp + c] = v; }, tid);
-    } else {
-      for (int q = tid; q < n_phi * rp; q += NT) fs[q] = up[q];
-      __syncthreads();
-      tile_product<C, NT>(
-          n_theta, rp, n_phi, [&](int i, int j) { return gs[i * n_phi + j]; },
-          [&](int j, int c) { return fs[j * rp + c]; }, [&](int i, int c, C v) { s1[i * rp + c] = v; }, tid);
-      __syncthreads();
-      for (int q = tid; q < n_theta * rt; q += NT) gs[q] = ut[q];
-      __syncthreads();
-      tile_product<C, NT>(
-          rt, rp, n_theta, [&](int a, int i) { return gs[i * rt + a]; }, [&](int i, int c) { return s1[i * rp + c]; },
-          [&](int a, int c, C v) { S2[a * rp + c] = v; }, tid);
-    }
+    for (int q = tid; q < Q; q += NT) S2[q] = gc(q);
   } else if (!it.theta_first) {
     // s1[a][j] = sum_i U^theta[i][a] conj(G[i][j])     (r_theta x n_phi)
-    tile_product<C, NT>(
-        rt, n_phi, n_theta, [&](int a, int i) { return ut[i * rt + a]; },
-        [&](int i, int j) { return conjc(Gi[(int64_t)(i * n_phi + j) * nrhs]); },
-        [&](int a, int j, C v) { s1[a * n_phi + j] = v; }, tid);
+    tile_product<T, NT>(
+        rt, n_phi, n_theta, [&](int a, int i) { return f.t(i, a); },
+        [&](int i, int j) { return gc(i * n_phi + j); }, [&](int a, int j, C v) { s1[a * n_phi + j] = v; }, tid);
     __syncthreads();
     // S[a][c] = sum_j s1[a][j] U^phi[j][c]
-    tile_product<C, NT>(
-        rt, rp, n_phi, [&](int a, int j) { return s1[a * n_phi + j]; }, [&](int j, int c) { return up[j * rp + c]; },
-        [&](int a, int c, C v) { S2[a * rp + c] = v; }, tid);
+    tile_product<T, NT>(
+        rt, rp, n_phi, [&](int a, int j) { return s1[a * n_phi + j]; },
+        [&](int j, int c) { return f.p(j, c); }, [&](int a, int c, C v) { S2[a * rp + c] = v; }, tid);
   } else {
     // s1[i][c] = sum_j conj(G[i][j]) U^phi[j][c]       (n_theta x r_phi)
-    tile_product<C, NT>(
-        n_theta, rp, n_phi, [&](int i, int j) { return conjc(Gi[(int64_t)(i * n_phi + j) * nrhs]); },
-        [&](int j, int c) { return up[j * rp + c]; }, [&](int i, int c, C v) { s1[i * rp + c] = v; }, tid);
+    tile_product<T, NT>(
+        n_theta, rp, n_phi, [&](int i, int j) { return gc(i * n_phi + j); },
+        [&](int j, int c) { return f.p(j, c); }, [&](int i, int c, C v) { s1[i * rp + c] = v; }, tid);
     __syncthreads();
     // S[a][c] = sum_i U^theta[i][a] s1[i][c]
-    tile_product<C, NT>(
-        rt, rp, n_theta, [&](int a, int i) { return ut[i * rt + a]; }, [&](int i, int c) { return s1[i * rp + c]; },
-        [&](int a, int c, C v) { S2[a * rp + c] = v; }, tid);
+    tile_product<T, NT>(
+        rt, rp, n_theta, [&](int a, int i) { return f.t(i, a); },
+        [&](int i, int c) { return s1[i * rp + c]; }, [&](int a, int c, C v) { S2[a * rp + c] = v; }, tid);
   }
-  for (int o = Q + tid; o < round_up(Q, E); o += NT) S2[o] = czero<C>();  // pack padding
+  for (int o = Q + tid; o < round_up(Q, Tr<T>::E); o += NT) S2[o] = czero<C>();  // pack padding
+}
+
+// q / d for 0 <= q < 2^20 (LDS holds fewer values), `inv` = 1 / d rounded: the quotient of
+// q + 1/2 is at least 1 / (2 d) from a whole number, more than the roundings of its size.
+__device__ __forceinline__ int quot(int q, int d, float inv) { return d == 1 ? q : (int)(((float)q + 0.5f) * inv); }
+
+// Copies parts of global memory to LDS with 64 bytes of loads in flight per thread, so
+// that everything a unit needs before its sweep costs about one memory latency:
+// x of the group (rows x0 ..; `nr` columns), conj(G) of the item's fibre and the angular
+// factors (rows of odd stride).  Null destinations are left out.
+template <typename T, int NT>
+__device__ __forceinline__ void stage_in(const typename Tr<T>::c* fac, const TuckItem& it, int n_theta, int n_phi,
+                                         int nrhs, const typename Tr<T>::c* x, int nr, typename Tr<T>::c* xs, int xrow,
+                                         const typename Tr<T>::c* g, typename Tr<T>::c* gs, typename Tr<T>::c* us) {
+  using C = typename Tr<T>::c;
+  const int tid = threadIdx.x;
+  const int rt = it.rt, rp = it.rp, ldt = rt | 1, ldp = rp | 1;
+  const int n_x = x ? it.nb * nr : 0, n_g = gs ? n_theta * n_phi : 0, n_t = us ? n_theta * rt : 0,
+            n_p = us ? n_phi * rp : 0;
+  const int e1 = n_x + n_g, e2 = e1 + n_t, total = e2 + n_p;
+  C* ups = us + round_up(n_theta * ldt, 2);
+  const C* ut = fac + it.off_ut - e1;
+  const C* up = fac + it.off_up - e2;
+  const C* xg = x + it.row0 * nrhs;
+  constexpr int U = 64 / sizeof(C);
+  for (int i0 = tid; i0 < total; i0 += U * NT) {
+    C v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = i0 + u * NT;
+      if (e < total) {
+        const int ex = quot(e, nr, 1.0f / nr);
+        const C* src = e < n_x  ? xg + (int64_t)ex * nrhs + (e - ex * nr)
+                       : e < e1 ? g + (int64_t)(e - n_x) * nrhs
+                       : e < e2 ? ut + e
+                                : up + e;
+        v[u] = *src;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = i0 + u * NT;
+      if (e < n_x) {
+        const int ex = quot(e, nr, 1.0f / nr);
+        xs[(e - ex * nr) * xrow + ex] = v[u];
+      } else if (e < e1) {
+        gs[e - n_x] = conjc(v[u]);
+      } else if (e < e2) {
+        const int q = e - e1, i = quot(q, rt, 1.0f / rt);
+        us[i * ldt + (q - i * rt)] = v[u];
+      } else if (e < total) {
+        const int q = e - e2, j = quot(q, rp, 1.0f / rp);
+        ups[j * ldp + (q - j * rp)] = v[u];
+      }
+    }
+  }
 }
 
 // Streaming phase over rows [b0, b1): s = core S (row-dots) with S in LDS region s2,
@@ -594,18 +631,19 @@ __device__ __forceinline__ void dis_stream(const typename Tr<T>::c* __restrict__
 // Aggregation of one work unit: a whole item (stream, angular phase, F written) or a
 // row block of a split item (its partial t stored for the finishing kernel).
 template <typename T, int NT>
-__device__ __forceinline__ void agg_unit(const typename Tr<T>::c* __restrict__ fac, const TuckItem* items,
-                                         const TuckUnit& u, const TuckSplit* splits, const Lds<T>& L,
+__device__ __forceinline__ void agg_unit(const typename Tr<T>::c* __restrict__ fac, const TuckWork& work,
+                                         const TuckSplit* splits, const Lds<T>& L,
                                          unsigned char* smem, int n_theta, int n_phi, int nrhs, int r,
                                          const typename Tr<T>::c* __restrict__ x, typename Tr<T>::c* __restrict__ F,
                                          typename Tr<T>::c* part, int64_t part_stride) {
   using C = typename Tr<T>::c;
-  const TuckItem it = items[u.item];
+  const TuckItem& it = work.it;
+  const TuckUnit& u = work.u;
   if (u.split < 0) {
     C* ts = reinterpret_cast<C*>(smem);  // t over x
     agg_stream<T, NT>(fac, it, L, smem, nrhs, r, x, 0, it.rb, ts);
     __syncthreads();
-    agg_angular<T, NT>(fac, it, L, smem, ts, n_theta, n_phi, nrhs, r, F);
+    agg_angular<T, NT>(it, global_angular<T>(fac, it), ts + L.r1, ts, n_theta, n_phi, nrhs, r, F);
   } else {
     const TuckSplit sp = splits[u.split];
     agg_stream<T, NT>(fac, it, L, smem, nrhs, r, x, u.b0, u.b1,
@@ -616,91 +654,583 @@ __device__ __forceinline__ void agg_unit(const typename Tr<T>::c* __restrict__ f
 // Disaggregation of one work unit: angular phase, then the stream over the unit's
 // rows; a whole item adds into V, a row block stores its partial v.
 template <typename T, int NT>
-__device__ __forceinline__ void dis_unit(const typename Tr<T>::c* __restrict__ fac, const TuckItem* items,
-                                         const TuckUnit& u, const TuckSplit* splits, const Lds<T>& L,
+__device__ __forceinline__ void dis_unit(const typename Tr<T>::c* __restrict__ fac, const TuckWork& work,
+                                         const TuckSplit* splits, const Lds<T>& L,
                                          unsigned char* smem, int n_theta, int n_phi, int nrhs, int r,
                                          const typename Tr<T>::c* __restrict__ G, typename Tr<T>::c* __restrict__ V,
                                          typename Tr<T>::c* part, int64_t part_stride) {
   using C = typename Tr<T>::c;
-  const TuckItem it = items[u.item];
+  const TuckItem& it = work.it;
+  const TuckUnit& u = work.u;
   C* dst = nullptr;
   if (u.split >= 0) {
     const TuckSplit sp = splits[u.split];
     dst = part + r * part_stride + sp.dis_off + (int64_t)u.sub * sp.nb_pad;
   }
-  dis_angular<T, NT>(fac, it, L, smem, n_theta, n_phi, nrhs, r, G, reinterpret_cast<C*>(smem) + L.s1, false, V);
+  C* s1 = reinterpret_cast<C*>(smem);
+  const C* Gi = G + ((int64_t)it.frow * n_theta * n_phi) * nrhs + r;
+  dis_angular<T, NT>(
+      it, global_angular<T>(fac, it), s1, n_theta, n_phi, [&](int q) { return conjc(Gi[(int64_t)q * nrhs]); }, s1 + L.s1);
   __syncthreads();
   dis_stream<T, NT>(fac, it, L, smem, nrhs, r, u.b0, u.b1, dst, V);
 }
 
 template <typename T, int NT>
 __global__ __launch_bounds__(NT) void tucker_agg_kernel(const typename Tr<T>::c* __restrict__ fac,
-                                                        const TuckItem* __restrict__ items,
-                                                        const TuckUnit* __restrict__ units,
-                                                        const TuckSplit* __restrict__ splits,
-                                                        const int32_t* __restrict__ order, TuckMax mx, int n_theta,
+                                                        const TuckWork* __restrict__ work,
+                                                        const TuckSplit* __restrict__ splits, TuckMax mx, int n_theta,
                                                         int n_phi, int nrhs,
                                                         const typename Tr<T>::c* __restrict__ x,
                                                         typename Tr<T>::c* __restrict__ F, typename Tr<T>::c* part,
                                                         int64_t part_stride) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const TuckUnit u = units[order[blockIdx.x]];
-  agg_unit<T, NT>(fac, items, u, splits, Lds<T>(mx), smem, n_theta, n_phi, nrhs, blockIdx.y, x, F,
+  const TuckWork w = work[blockIdx.x];
+  agg_unit<T, NT>(fac, w, splits, Lds<T>(mx), smem, n_theta, n_phi, nrhs, blockIdx.y, x, F,
                   part, part_stride);
 }
 
 template <typename T, int NT>
 __global__ __launch_bounds__(NT) void tucker_dis_kernel(const typename Tr<T>::c* __restrict__ fac,
-                                                        const TuckItem* __restrict__ items,
-                                                        const TuckUnit* __restrict__ units,
-                                                        const TuckSplit* __restrict__ splits,
-                                                        const int32_t* __restrict__ order, TuckMax mx, int n_theta,
+                                                        const TuckWork* __restrict__ work,
+                                                        const TuckSplit* __restrict__ splits, TuckMax mx, int n_theta,
                                                         int n_phi, int nrhs,
                                                         const typename Tr<T>::c* __restrict__ G,
                                                         typename Tr<T>::c* __restrict__ V, typename Tr<T>::c* part,
                                                         int64_t part_stride) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const TuckUnit u = units[order[blockIdx.x]];
-  dis_unit<T, NT>(fac, items, u, splits, Lds<T>(mx), smem, n_theta, n_phi, nrhs, blockIdx.y, G, V,
+  const TuckWork w = work[blockIdx.x];
+  dis_unit<T, NT>(fac, w, splits, Lds<T>(mx), smem, n_theta, n_phi, nrhs, blockIdx.y, G, V,
                   part, part_stride);
 }
 
-// One launch for a whole aggregation + disaggregation pass: work-list entry e is
-// the aggregation of unit e if e >= 0 and the disaggregation of unit ~e otherwise.
-// Both stages' units interleave in one longest-first list, so small units of either
-// stage fill the end of the launch.  The launch is persistent: as many workgroups as
-// the CUs hold at once, each taking the next entry (of n_list per right-hand side) from
-// the work counter `next`, which the V-zeroing kernel before it sets to zero.  On
-// layouts of many small units this keeps every CU full; with one workgroup per entry
-// the hardware refilled a CU's free slot only tens of microseconds after a unit ended.
-template <typename T, int NT>
-__global__ __launch_bounds__(NT) void tucker_pass_kernel(const typename Tr<T>::c* __restrict__ fac,
-                                                         const TuckItem* __restrict__ items,
-                                                         const TuckUnit* __restrict__ units,
-                                                         const TuckSplit* __restrict__ splits,
-                                                         const int32_t* __restrict__ list, int n_list, TuckMax mx,
-                                                         int n_theta, int n_phi, int nrhs,
-                                                         const typename Tr<T>::c* __restrict__ x,
-                                                         typename Tr<T>::c* __restrict__ F,
-                                                         const typename Tr<T>::c* __restrict__ G,
-                                                         typename Tr<T>::c* __restrict__ V, typename Tr<T>::c* part,
-                                                         int64_t part_stride, int32_t* __restrict__ next) {
+// ------------------------------------------------------------ row-streaming kernels
+//
+// One sweep over the rows b of an item's factors serves both stages.  Row b of
+// U^beta^T and row b of the core take part in
+//   y[b] = U_b . x,   t += core_b y[b]        (aggregation)
+//   s[b] = core_b . S,   v += U_b s[b]        (disaggregation)
+// and every product above needs only row b, so a pass reads each factor once, not once
+// per stage.  A row's packs (U_b first, then core_b) are cut into slices of 64; slice
+// w + NW j belongs to wavefront w (NW wavefronts), whose lanes hold one pack each of
+// the KR rows in work and of the KR rows being loaded, the matching packs of x or S and
+// the running sums of v or t in registers.  Per KR rows the dot products are summed
+// over the wavefront by a halving exchange (each step adds and halves the values a lane
+// carries), over the wavefronts through LDS (one barrier), and return as wavefront-
+// uniform scalars for the axpy.
+//
+// The sweep is bound by HBM.  A stage alone runs the same code with the other stage's
+// vector zero, so a pass equals its two stages bit for bit.
+
+// Sum of v and its partner lane across lane bit BIT (BIT = 4 pairs lanes i and 7 - i of
+// eight, which later steps over bits 2 and 1 complete to the same sums).
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+}
+template <int BIT>
+__device__ __forceinline__ uint32_t partner(uint32_t v) {
+  static_assert(BIT == 8 || BIT == 4 || BIT == 2 || BIT == 1, "within a row of 16 lanes");
+  constexpr int ctrl = BIT == 8 ? 0x128 /* row_ror:8 */ : BIT == 4 ? 0x141 /* row_half_mirror */
+                       : BIT == 2 ? 0x4E /* quad_perm 2,3,0,1 */ : 0xB1 /* quad_perm 1,0,3,2 */;
+  return dpp_u32<ctrl>(v);
+}
+template <int BIT>
+__device__ __forceinline__ float partner(float v) {
+  return __uint_as_float(partner<BIT>(__float_as_uint(v)));
+}
+template <int BIT>
+__device__ __forceinline__ double partner(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = partner<BIT>((uint32_t)u), hi = partner<BIT>((uint32_t)(u >> 32));
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+// The value of the lane 4 further on in the row of 16.
+__device__ __forceinline__ float rotate4(float v) { return __uint_as_float(dpp_u32<0x124>(__float_as_uint(v))); }
+__device__ __forceinline__ double rotate4(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = dpp_u32<0x124>((uint32_t)u), hi = dpp_u32<0x124>((uint32_t)(u >> 32));
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+// v_permlane32_swap (v_permlane16_swap) exchanges the upper half (odd rows of 16) of a
+// with the lower half (even rows) of b.
+template <int BIT>
+__device__ __forceinline__ void lane_swap(uint32_t& a, uint32_t& b) {
+  typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+  u2 r;
+  if constexpr (BIT == 32)
+    r = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(a, b, false, false));
+  else
+    r = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(a, b, false, false));
+  a = r[0];
+  b = r[1];
+}
+template <int BIT>
+__device__ __forceinline__ float swap_add(float a, float b) {
+  uint32_t x = __float_as_uint(a), y = __float_as_uint(b);
+  lane_swap<BIT>(x, y);
+  return __uint_as_float(x) + __uint_as_float(y);
+}
+template <int BIT>
+__device__ __forceinline__ double swap_add(double a, double b) {
+  const uint64_t u = (uint64_t)__double_as_longlong(a), w = (uint64_t)__double_as_longlong(b);
+  uint32_t al = (uint32_t)u, ah = (uint32_t)(u >> 32), bl = (uint32_t)w, bh = (uint32_t)(w >> 32);
+  lane_swap<BIT>(al, bl);
+  lane_swap<BIT>(ah, bh);
+  return __longlong_as_double((long long)(((uint64_t)ah << 32) | al)) +
+         __longlong_as_double((long long)(((uint64_t)bh << 32) | bl));
+}
+// Lanes with bit BIT clear receive a's sum over the lane pair, lanes with it set b's.
+template <int BIT, typename T>
+__device__ __forceinline__ T fold2(T a, T b, int lane) {
+  if constexpr (BIT >= 16) {
+    return swap_add<BIT>(a, b);
+  } else {
+    const bool up = lane & BIT;
+    const T keep = up ? b : a, send = up ? a : b;
+    return keep + partner<BIT>(send);
+  }
+}
+template <int BIT, typename T>
+__device__ __forceinline__ T pair_add(T v) {
+  if constexpr (BIT >= 16)
+    return swap_add<BIT>(v, v);
+  else
+    return v + partner<BIT>(v);
+}
+// Sums of v[0 .. NV) (NV a power of two, at most 64) over the wavefront: lane l returns
+// the total of value l / (64 / NV).
+template <int NV, int BIT, typename T>
+__device__ __forceinline__ T wave_fold(T (&v)[NV], int lane) {
+  if constexpr (NV > 1) {
+    T h[NV / 2];
+#pragma unroll
+    for (int i = 0; i < NV / 2; ++i) h[i] = fold2<BIT>(v[i], v[i + NV / 2], lane);
+    return wave_fold<NV / 2, BIT / 2>(h, lane);
+  } else if constexpr (BIT >= 1) {
+    T h[1] = {pair_add<BIT>(v[0])};
+    return wave_fold<1, BIT / 2>(h, lane);
+  } else {
+    return v[0];
+  }
+}
+// Sum over the lanes that differ in the bits from FROM (4 or more) up to 32.  (In a row of
+// 16, rotations by 4 and then by 8 reach the four lanes equal in bits 1 and 0.)
+template <int FROM, typename T>
+__device__ __forceinline__ T high_add(T v) {
+  static_assert(FROM >= 4, "the rotation by 4 keeps bits 1 and 0");
+  if constexpr (FROM == 4)
+    return high_add<8>(v + rotate4(v));
+  else if constexpr (FROM < 64)
+    return high_add<FROM * 2>(pair_add<FROM>(v));
+  else
+    return v;
+}
+__device__ __forceinline__ float lane_value(float v, int lane) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), lane));
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// LDS of a row-streaming workgroup (complex elements; red in bytes):
+//   vec    [RB][row]  x (padded to whole packs), then S of the disaggregation, later t
+//   inter  the angular intermediate of either stage
+//   gs     staged conj(G) of one right-hand side, us the staged angular factors (0 unstaged)
+//   red    the wavefronts' partial dot products, double buffered
+template <typename T>
+struct StreamLds {
+  int vecs, row, inter, gs, us, red;
+  static constexpr int kRedValues = 16;  // dot products of a step per right-hand side, at most
+  __host__ __device__ __forceinline__ StreamLds(const TuckMax& mx, int nw, int rb, bool staged, bool dis)
+      : vecs(rb),
+        row(round_up(mx.row, 2)),
+        inter(round_up(mx.t3, 2)),
+        gs(staged && dis ? round_up(mx.nt * mx.np, 2) : 0),
+        us(staged ? staged_factors(mx) : 0),
+        red(nw > 1 ? 2 * nw * kRedValues * rb * (int)sizeof(T) : 0) {}
+  static __host__ __device__ __forceinline__ int staged_factors(const TuckMax& mx) {
+    return round_up(mx.nt * (mx.rt | 1), 2) + round_up(mx.np * (mx.rp | 1), 2);
+  }
+  __host__ __device__ size_t bytes() const {
+    return ((size_t)vecs * row + inter + gs + us) * sizeof(typename Tr<T>::c) + red;
+  }
+};
+
+// Rows per step, and steps whose rows are held (one in work, the others being loaded), for
+// J slices per wavefront: 48 to 64 registers of row data a lane, so that a workgroup keeps
+// at least 24 KB of loads in flight.
+constexpr int rows_per_step(int J) { return J == 1 ? 4 : (J == 2 ? 2 : 1); }
+constexpr int steps_held(int J, int RB, bool f64) { return J > 4 ? 2 : (J == 4 ? (f64 ? 2 : 3) : 3); }
+
+__device__ __forceinline__ float4 pkeep(float4 v, bool k) {
+  return make_float4(k ? v.x : 0.f, k ? v.y : 0.f, k ? v.z : 0.f, k ? v.w : 0.f);
+}
+__device__ __forceinline__ double2 pkeep(double2 v, bool k) { return make_double2(k ? v.x : 0.0, k ? v.y : 0.0); }
+
+// If `now`: d[0] takes the running sum d[1], which starts again from zero.
+template <typename C>
+__device__ __forceinline__ void restart(C (&d)[2], bool now) {
+  d[0].x = now ? d[1].x : d[0].x;
+  d[0].y = now ? d[1].y : d[0].y;
+  d[1].x = now ? 0 : d[1].x;
+  d[1].y = now ? 0 : d[1].y;
+}
+
+// The sweep over rows [b0, b1) with J slices per wavefront.  `ub` and `cb`: row 0 of
+// U^beta^T and of the core (npu and npc packs per row); vec: the RB vectors in LDS, vrow packs apart.  On return acc[r][j] of lane l holds pack
+// l of slice w + NW j of [v | t] for right-hand side r.
+template <typename T, int NT, int J, int RB>
+__device__ __forceinline__ void sweep_rows(const typename Tr<T>::pack* ub, const typename Tr<T>::pack* cb, int npu,
+                                           int npc, int b0, int b1,
+                                           const typename Tr<T>::pack* vec, int vrow, T* red, int wave, int lane,
+                                           typename Tr<T>::pack (&acc)[RB][J]) {
+  using C = typename Tr<T>::c;
+  using P = typename Tr<T>::pack;
+  constexpr int NW = NT / 64;
+  constexpr int KR = rows_per_step(J), D = steps_held(J, RB, sizeof(T) == 8);
+  constexpr int NV = 4 * KR * RB;
+  constexpr bool kVecRegs = RB == 1 && J <= 4;
+  constexpr int kAux = NT >= 256 ? 2 : 0;  // non-temporal
+  static_assert(NV <= 64 && NV <= StreamLds<T>::kRedValues * RB, "dot products per step");
+  const int nsu = (npu + 63) >> 6, ns = nsu + ((npc + 63) >> 6);
+
+  // slice j of this wavefront and this lane's pack in it; a slice beyond the row repeats the
+  // wavefront's first one and, like a lane beyond the row, meets a zero vector.  All but
+  // the lane offsets is wavefront-uniform and the step has no branch: buffer loads take
+  // the item's base, a 32-bit lane offset and a scalar row offset, and the waits for them
+  // count exactly.
+  uint32_t ld[J], off[J];
+  int voff[J];
+  bool isu[J], live[J];
+  const uint64_t at = (uint64_t)ub;
+  const uint64_t at0 = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at) |
+                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32)) << 32;
+  const auto rows = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(at0), 0, -1, 0x00027000);
+  const uint32_t core = (uint32_t)((uint64_t)cb - at);
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    int s = wave + NW * j;
+    const bool in = s < ns;
+    s = in ? s : (wave < ns ? wave : 0);
+    const bool u = s < nsu;
+    isu[j] = in && u;
+    const int p = 64 * (u ? s : s - nsu) + lane, np = u ? npu : npc;
+    ld[j] = (uint32_t)np * sizeof(P);
+    const int q = min(p, np - 1);
+    off[j] = (uint32_t)q * sizeof(P) + (u ? 0u : core);
+    live[j] = in && p < np;
+    voff[j] = q + (u ? 0 : npu);
+  }
+  // first core slice of the wavefront: the sum over slices restarts there
+  int jc = 0;
+#pragma unroll
+  for (int j = 0; j < J; ++j) jc += isu[j] ? 1 : 0;
+  P xv[kVecRegs ? J : 1];
+  if constexpr (kVecRegs) {
+#pragma unroll
+    for (int j = 0; j < J; ++j) xv[j] = live[j] ? vec[voff[j]] : pzero<P>();
+  }
+#pragma unroll
+  for (int r = 0; r < RB; ++r)
+#pragma unroll
+    for (int j = 0; j < J; ++j) acc[r][j] = pzero<P>();
+
+  auto load = [&](P (&u)[KR][J], int b) {
+#pragma unroll
+    for (int k = 0; k < KR; ++k) {
+      const uint32_t row = (uint32_t)min(b + k, b1 - 1);  // (rows past the end are loaded, not used)
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+        u[k][j] = __builtin_bit_cast(P, __builtin_amdgcn_raw_buffer_load_b128(rows, off[j], row * ld[j], kAux));
+    }
+  };
+  int par = 0;
+  auto step = [&](const P (&u)[KR][J], int b) {
+    C d[KR][RB][2];  // dot products of the row with x (U_b) and S (core_b)
+#pragma unroll
+    for (int k = 0; k < KR; ++k)
+#pragma unroll
+      for (int r = 0; r < RB; ++r) d[k][r][0] = d[k][r][1] = czero<C>();
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      P xr[RB];
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        if constexpr (kVecRegs) {
+          xr[r] = xv[j];
+        } else {
+          xr[r] = pkeep(vec[r * vrow + voff[j]], live[j]);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < KR; ++k)
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+          if (j > 0) restart(d[k][r], j == jc);  // U_b's sum up to slice jc, then core_b's
+          pdot(d[k][r][1], u[k][j], xr[r]);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < KR; ++k)
+#pragma unroll
+      for (int r = 0; r < RB; ++r) restart(d[k][r], jc == J);
+    T v[NV];
+#pragma unroll
+    for (int k = 0; k < KR; ++k)
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          v[((k * RB + r) * 2 + m) * 2] = d[k][r][m].x;
+          v[((k * RB + r) * 2 + m) * 2 + 1] = d[k][r][m].y;
+        }
+    T tot = wave_fold<NV, 32>(v, lane);
+    constexpr int kSpan = 64 / NV;  // lanes per value
+    int stride = kSpan;
+    if constexpr (NW > 1) {
+      T* rd = red + par * NW * NV;
+      par ^= 1;
+      if (lane % kSpan == 0) rd[wave * NV + lane / kSpan] = tot;
+      __syncthreads();
+      tot = T(0);
+#pragma unroll
+      for (int w0 = 0; w0 < NW; w0 += kSpan) {
+        const int w = w0 + lane / NV;
+        const T part = rd[min(w, NW - 1) * NV + lane % NV];
+        tot += w < NW ? part : T(0);
+      }
+      tot = high_add<NV>(tot);
+      stride = 1;
+    }
+#pragma unroll
+    for (int k = 0; k < KR; ++k) {
+      const bool in = b + k < b1;
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        const int i = (k * RB + r) * 4;
+        C y = {lane_value(tot, i * stride), lane_value(tot, (i + 1) * stride)};
+        C sv = {lane_value(tot, (i + 2) * stride), lane_value(tot, (i + 3) * stride)};
+        if (KR > 1) {
+          y = {in ? y.x : 0, in ? y.y : 0};
+          sv = {in ? sv.x : 0, in ? sv.y : 0};
+        }
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+          const C c = {j < jc ? sv.x : y.x, j < jc ? sv.y : y.y};
+          paxpy(acc[r][j], u[k][j], c);
+        }
+      }
+    }
+  };
+  P u[D][KR][J];
+#pragma unroll
+  for (int i = 0; i + 1 < D; ++i) {
+    load(u[i], b0 + i * KR);
+    __builtin_amdgcn_sched_barrier(0);  // in step order, so that the waits in the loop are exact
+  }
+  for (int b = b0; b < b1;) {
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+      load(u[(i + D - 1) % D], b + (D - 1) * KR);
+      step(u[i], b);
+      b += KR;
+      if (b >= b1) break;
+    }
+  }
+}
+
+template <typename T>
+struct StreamArgs {
+  const typename Tr<T>::c* fac;
+  const TuckWork* work;
+  const TuckSplit* splits;
+  int n_units, n_theta, n_phi, nrhs, rstep, n_rblk;
+  TuckMax mx;
+  int staged;
+  const typename Tr<T>::c* x;  // nullptr: no aggregation
+  typename Tr<T>::c* F;
+  const typename Tr<T>::c* G;  // nullptr: no disaggregation
+  typename Tr<T>::c* V;
+  typename Tr<T>::c* part;
+  int64_t part_stride;
+  int32_t* next;  // work counter of a persistent launch (nullptr: one workgroup per entry)
+};
+
+// The sweep and its outputs: t to LDS (`vec`'s S region; a split item's row block stores
+// it as its partial sums), conj(v) added to V (or stored as partial sums).
+template <typename T, int NT, int J, int RB>
+__device__ __forceinline__ void sweep_unit(const StreamArgs<T>& a, const TuckItem& it, const TuckUnit& u, int r0,
+                                           int nr, typename Tr<T>::c* vec, int vrow, T* red) {
+  using C = typename Tr<T>::c;
+  using P = typename Tr<T>::pack;
+  constexpr int E = Tr<T>::E, NW = NT / 64;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int npu = it.ld_ub / E, npc = it.ld_c / E;
+  const int nsu = (npu + 63) >> 6, ns = nsu + ((npc + 63) >> 6);
+  const bool agg = a.x != nullptr, dis = a.G != nullptr;
+  P acc[RB][J];
+  sweep_rows<T, NT, J, RB>(reinterpret_cast<const P*>(a.fac + it.off_ubt),
+                           reinterpret_cast<const P*>(a.fac + it.off_core), npu, npc, u.b0, u.b1,
+                           reinterpret_cast<const P*>(vec), vrow / E, red, wave, lane, acc);
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int s = wave + NW * j;
+    if (s >= ns) break;
+    const bool isu = s < nsu;
+    const int p = 64 * (isu ? s : s - nsu) + lane;
+    if (p >= (isu ? npu : npc) || !(isu ? dis : agg)) continue;
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+      if (r >= nr) break;
+      if (u.split >= 0) {
+        const TuckSplit sp = a.splits[u.split];
+        const int64_t v_at = sp.dis_off + (int64_t)u.sub * sp.nb_pad, t_at = sp.agg_off + (int64_t)u.sub * sp.q_pad;
+        C* dst = a.part + (r0 + r) * a.part_stride + (isu ? v_at : t_at);
+        reinterpret_cast<P*>(dst)[p] = acc[r][j];
+      } else if (!isu) {
+        reinterpret_cast<P*>(vec + r * vrow + it.ld_ub)[p] = acc[r][j];
+      } else {
+        const C* vals = reinterpret_cast<const C*>(&acc[r][j]);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const int n = p * E + e;
+          if (n < it.nb) atomic_add_c(a.V + (it.row0 + n) * a.nrhs + r0 + r, conjc(vals[e]));
+        }
+      }
+    }
+  }
+}
+
+// *p through the scalar cache, for a uniform p: what it points at is constant while kernels
+// run.
+__device__ __forceinline__ TuckWork const_load(const TuckWork* p) {
+  struct Words {
+    uint32_t w[sizeof(TuckWork) / 4];
+  } v;
+  typedef const uint32_t __attribute__((address_space(4))) * Const;
+  const Const c = (Const)(uint64_t)p;
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(TuckWork) / 4; ++i) v.w[i] = c[i];
+  return __builtin_bit_cast(TuckWork, v);
+}
+
+// One work entry: a unit and a block of at most RB right-hand sides.  The entries of a
+// unit follow each other, so that the second and later blocks find the factors in the
+// memory-side cache.
+template <typename T, int NT, int JMAX, int RB>
+__device__ __forceinline__ void stream_entry(const StreamArgs<T>& a, const StreamLds<T>& L, unsigned char* smem,
+                                             int entry, int32_t& next_entry) {
+  using C = typename Tr<T>::c;
+  constexpr int E = Tr<T>::E, NW = NT / 64;
+  const int tid = threadIdx.x;
+  const int iu = entry / a.n_rblk, blk = entry - iu * a.n_rblk;
+  // (the list is constant while kernels run: scalar loads)
+  const TuckWork work = const_load(a.work + iu);
+  const TuckUnit& u = work.u;
+  const TuckItem& it = work.it;
+  const int r0 = blk * a.rstep, nr = min(a.rstep, a.nrhs - r0);
+  C* vec = reinterpret_cast<C*>(smem);
+  C* inter = vec + RB * L.row;
+  C* gs = inter + L.inter;
+  C* us = gs + L.gs;
+  T* red = reinterpret_cast<T*>(us + L.us);
+  const bool staged = a.staged && !it.ident;
+  const C* Gi = a.G ? a.G + ((int64_t)it.frow * a.n_theta * a.n_phi) * a.nrhs + r0 : nullptr;
+  stage_in<T, NT>(a.fac, it, a.n_theta, a.n_phi, a.nrhs, a.x ? a.x + r0 : nullptr, nr, vec, L.row, Gi,
+                  staged && a.G ? gs : nullptr, staged && (a.G || u.split < 0) ? us : nullptr);
+  // zeros: x's padding to whole packs (all of it without an aggregation), absent columns
+  for (int r = 0; r < RB; ++r) {
+    C* v = vec + r * L.row;
+    const bool col = r < nr;
+    for (int n = (col && a.x ? it.nb : 0) + tid; n < it.ld_ub; n += NT) v[n] = czero<C>();
+    if (!col || !a.G)
+      for (int q = tid; q < it.ld_c; q += NT) v[it.ld_ub + q] = czero<C>();
+  }
+  __syncthreads();
+  if (a.G) {
+    for (int r = 0; r < nr; ++r) {
+      C* S = vec + r * L.row + it.ld_ub;
+      if (r > 0) {  // the previous column's products have read their operands
+        __syncthreads();
+        if (staged) {
+          stage_in<T, NT>(a.fac, it, a.n_theta, a.n_phi, a.nrhs, nullptr, 1, nullptr, 0, Gi + r, gs, nullptr);
+          __syncthreads();
+        }
+      }
+      if (staged)
+        dis_angular<T, NT>(
+            it, staged_angular<T>(us, it, a.n_theta), inter, a.n_theta, a.n_phi, [&](int q) { return gs[q]; }, S);
+      else
+        dis_angular<T, NT>(
+            it, global_angular<T>(a.fac, it), inter, a.n_theta, a.n_phi, [&](int q) { return conjc(Gi[(int64_t)q * a.nrhs + r]); }, S);
+    }
+    __syncthreads();
+  }
+  const int ns = ((it.ld_ub / E + 63) >> 6) + ((it.ld_c / E + 63) >> 6);
+  const int j = (ns + NW - 1) / NW;
+  if constexpr (JMAX == 4) {
+    if (j <= 1)
+      sweep_unit<T, NT, 1, RB>(a, it, u, r0, nr, vec, L.row, red);
+    else if (j == 2)
+      sweep_unit<T, NT, 2, RB>(a, it, u, r0, nr, vec, L.row, red);
+    else if (j == 3)
+      sweep_unit<T, NT, 3, RB>(a, it, u, r0, nr, vec, L.row, red);
+    else
+      sweep_unit<T, NT, 4, RB>(a, it, u, r0, nr, vec, L.row, red);
+  } else {
+    if (j <= 2)
+      sweep_unit<T, NT, 2, RB>(a, it, u, r0, nr, vec, L.row, red);
+    else if (j <= 4)
+      sweep_unit<T, NT, 4, RB>(a, it, u, r0, nr, vec, L.row, red);
+    else if (j <= 6 || JMAX == 8)
+      sweep_unit<T, NT, JMAX == 8 ? 8 : 6, RB>(a, it, u, r0, nr, vec, L.row, red);
+    else if (j <= 10)
+      sweep_unit<T, NT, 10, RB>(a, it, u, r0, nr, vec, L.row, red);
+    else
+      sweep_unit<T, NT, 16, RB>(a, it, u, r0, nr, vec, L.row, red);
+  }
+  if (a.next && tid == 0) next_entry = atomicAdd(a.next, 1);
+  if (a.x == nullptr || u.split >= 0) return;
+  for (int r = 0; r < nr; ++r) {
+    __syncthreads();
+    const C* ts = vec + r * L.row + it.ld_ub;
+    if (staged)
+      agg_angular<T, NT>(it, staged_angular<T>(us, it, a.n_theta), inter, ts, a.n_theta, a.n_phi, a.nrhs, r0 + r, a.F);
+    else
+      agg_angular<T, NT>(it, global_angular<T>(a.fac, it), inter, ts, a.n_theta, a.n_phi, a.nrhs, r0 + r, a.F);
+  }
+}
+
+// A pass is persistent: as many workgroups as the CUs hold at once, each taking the next
+// entry of the longest-first list from the work counter, which the V-zeroing kernel
+// before it sets to zero (with one workgroup per entry the hardware refilled a CU's free
+// slot only tens of microseconds after a unit of a small-box layout ended).  A stage
+// alone runs one workgroup per entry.
+template <typename T, int NT, int JMAX, int RB>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(JMAX == 4 && RB == 1 ? 4 : 2)))
+void tucker_pass_kernel(StreamArgs<T> a) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int32_t take;
-  const Lds<T> L(mx);
-  const int total = n_list * nrhs;
+  const StreamLds<T> L(a.mx, NT / 64, RB, a.staged, a.G != nullptr);
+  const int total = a.n_units * a.n_rblk;
+  if (a.next == nullptr) {
+    int32_t none;
+    stream_entry<T, NT, JMAX, RB>(a, L, smem, blockIdx.x, none);
+    return;
+  }
+  int32_t mine = 0;  // (first thread) the next entry, taken when the current one's sweep is done
+  if (threadIdx.x == 0) mine = atomicAdd(a.next, 1);
   for (;;) {
-    if (threadIdx.x == 0) take = atomicAdd(next, 1);
+    if (threadIdx.x == 0) take = mine;
     __syncthreads();
-    const int i = take;
+    const int i = __builtin_amdgcn_readfirstlane(take);
     if (i >= total) break;  // uniform: every wavefront leaves
-    const int r = i / n_list;
-    const int32_t e = list[i - r * n_list];
-    if (e >= 0)
-      agg_unit<T, NT>(fac, items, units[e], splits, L, smem, n_theta, n_phi, nrhs, r, x, F, part, part_stride);
-    else
-      dis_unit<T, NT>(fac, items, units[~e], splits, L, smem, n_theta, n_phi, nrhs, r, G, V, part, part_stride);
-    __syncthreads();  // the unit's last LDS reads and `take` are done before the next entry
+    stream_entry<T, NT, JMAX, RB>(a, L, smem, i, mine);
+    __syncthreads();  // the entry's last LDS reads and `take` are done before the next one
   }
 }
 
@@ -708,14 +1238,22 @@ __global__ __launch_bounds__(NT) void tucker_pass_kernel(const typename Tr<T>::c
 // partial t of split entry blockIdx.x (in block order, so the result does not depend
 // on the schedule) and run the angular phase into F; blocks [n_agg, gridDim.x) sum
 // the partial v of split entry blockIdx.x - n_agg and add conj(v) to V.
-template <typename T, int NT>
-__global__ __launch_bounds__(NT) void tucker_finish_kernel(const typename Tr<T>::c* __restrict__ fac,
-                                                           const TuckItem* __restrict__ items,
-                                                           const TuckSplit* __restrict__ splits, int n_agg,
-                                                           TuckMax mx, int n_theta, int n_phi, int nrhs,
-                                                           const typename Tr<T>::c* __restrict__ part,
-                                                           int64_t part_stride, typename Tr<T>::c* __restrict__ F,
-                                                           typename Tr<T>::c* __restrict__ V) {
+constexpr int kFinishThreads = 512;
+template <typename T>
+struct FinishLds {
+  int q, inter, stage;
+  __host__ __device__ __forceinline__ FinishLds(const TuckMax& mx, bool staged)
+      : q(round_up(round_up(mx.q, Tr<T>::E), 2)),
+        inter(round_up(mx.t3, 2)),
+        stage(staged ? StreamLds<T>::staged_factors(mx) : 0) {}
+  __host__ __device__ size_t bytes() const { return ((size_t)q + inter + stage) * sizeof(typename Tr<T>::c); }
+};
+template <typename T>
+__global__ __launch_bounds__(kFinishThreads) void tucker_finish_kernel(
+    const typename Tr<T>::c* __restrict__ fac, const TuckItem* __restrict__ items,
+    const TuckSplit* __restrict__ splits, int n_agg, TuckMax mx, int staged, int n_theta, int n_phi, int nrhs,
+    const typename Tr<T>::c* __restrict__ part, int64_t part_stride, typename Tr<T>::c* __restrict__ F,
+    typename Tr<T>::c* __restrict__ V) {
   using C = typename Tr<T>::c;
   constexpr int E = Tr<T>::E;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -725,9 +1263,13 @@ __global__ __launch_bounds__(NT) void tucker_finish_kernel(const typename Tr<T>:
   const TuckItem it = items[sp.item];
   const C* base = part + r * part_stride;
   if (agg) {
+    const FinishLds<T> L(mx, staged);
     const int Q = it.rt * it.rp;
     C* ts = reinterpret_cast<C*>(smem);
-    for (int q = tid; q < round_up(Q, E); q += NT) {
+    if (L.stage && !it.ident)
+      stage_in<T, kFinishThreads>(fac, it, n_theta, n_phi, nrhs, nullptr, 1, nullptr, 0, nullptr, nullptr,
+                                  ts + L.q + L.inter);
+    for (int q = tid; q < round_up(Q, E); q += kFinishThreads) {
       C acc = czero<C>();
       if (q < Q)
         for (int s = 0; s < sp.n_parts; ++s) {
@@ -738,10 +1280,14 @@ __global__ __launch_bounds__(NT) void tucker_finish_kernel(const typename Tr<T>:
       ts[q] = acc;
     }
     __syncthreads();
-    agg_angular<T, NT>(fac, it, Lds<T>(mx), smem, ts, n_theta, n_phi, nrhs, r, F);
+    C* inter = ts + L.q;
+    if (L.stage && !it.ident)
+      agg_angular<T, kFinishThreads>(it, staged_angular<T>(inter + L.inter, it, n_theta), inter, ts, n_theta, n_phi, nrhs, r, F);
+    else
+      agg_angular<T, kFinishThreads>(it, global_angular<T>(fac, it), inter, ts, n_theta, n_phi, nrhs, r, F);
   } else {
     C* Vo = V + it.row0 * nrhs + r;
-    for (int n = tid; n < it.nb; n += NT) {
+    for (int n = tid; n < it.nb; n += kFinishThreads) {
       C acc = czero<C>();
       for (int s = 0; s < sp.n_parts; ++s) {
         const C v = base[sp.dis_off + (int64_t)s * sp.nb_pad + n];
@@ -794,6 +1340,7 @@ __global__ __launch_bounds__(256) void zero_rows_kernel(C* __restrict__ base, co
 
 }  // namespace
 
+#ifndef TUCKFMM_STREAM_F64
 hipError_t launch_zero_rows(size_t elem_bytes, void* base, const int32_t* rows, int n_rows, int64_t row_elems,
                             hipStream_t s) {
   if (n_rows <= 0 || row_elems <= 0) return hipSuccess;
@@ -808,126 +1355,173 @@ hipError_t launch_zero_rows(size_t elem_bytes, void* base, const int32_t* rows, 
     return hipErrorInvalidValue;
   return hipGetLastError();
 }
+#endif
 
+// Kernel of a fit (see stream_fits).
+#define TFMM_STREAM_CASE(nt, jm, r)                            \
+  if (f.threads == nt && f.jmax == jm && f.rb == r) {          \
+    constexpr int NT = nt, JMAX = jm, RB = r;                  \
+    return launch_stream_kernel<T, NT, JMAX, RB>(a, f, entries, s); \
+  }
+
+// The general kernels' LDS.
 template <typename T>
 size_t tucker_lds_bytes(const TuckMax& mx) {
   return Lds<T>(mx).bytes();
 }
 
-// Workgroup sizes a launch may take.
-#define TFMM_NT_SWITCH(threads, ...) \
-  switch (threads) {                  \
-    case 64: {                        \
-      constexpr int NT = 64;          \
-      __VA_ARGS__;                    \
-      break;                          \
-    }                                 \
-    case 128: {                       \
-      constexpr int NT = 128;         \
-      __VA_ARGS__;                    \
-      break;                          \
-    }                                 \
-    case 256: {                       \
-      constexpr int NT = 256;         \
-      __VA_ARGS__;                    \
-      break;                          \
-    }                                 \
-    case 512: {                       \
-      constexpr int NT = 512;         \
-      __VA_ARGS__;                    \
-      break;                          \
-    }                                 \
-    default:                          \
-      return hipErrorInvalidValue;    \
+// The row-streaming kernel for workgroups of `threads` (more where the longest row needs
+// them) and nrhs right-hand sides; false if a row is too long for it or its LDS beyond
+// mx.lds (the general kernels run the layout then).  A wavefront's lanes hold up to 4
+// slices of 64 packs in the kernels of 128 registers; longer rows take 8 or, with 512
+// threads, 16.  2 or 4 right-hand sides share a read of the factors where the row allows
+// 4 slices.  The angular operands are staged in LDS while a CU still holds
+// kStageMinWaves wavefronts.
+template <typename T>
+bool stream_fits(const TuckMax& mx, int threads, int nrhs, bool dis, StreamFit* out) {
+  for (; threads <= 512; threads *= 2) {
+    const int nw = threads / 64, j = (mx.slices + nw - 1) / nw;
+    const int jmax = j <= 4 ? 4 : (j <= 8 ? 8 : (j <= 16 && threads == 512 ? 16 : 0));
+    if (!jmax) continue;
+    for (int rb = jmax == 4 && nrhs > 1 ? (nrhs == 2 ? 2 : 4) : 1; rb >= 1; rb /= 2) {
+      const size_t staged = StreamLds<T>(mx, nw, rb, true, dis).bytes();
+      const size_t plain = StreamLds<T>(mx, nw, rb, false, dis).bytes();
+      if (plain > (size_t)mx.lds) continue;
+      out->threads = threads;
+      out->jmax = jmax;
+      out->rb = rb;
+      out->staged = mx.stage && staged <= (size_t)mx.lds && (int)(kCuLds / staged) * nw >= kStageMinWaves;
+      out->lds = out->staged ? staged : plain;
+      return true;
+    }
   }
+  return false;
+}
+
+template <typename T, int NT, int JMAX, int RB>
+hipError_t launch_stream_kernel(const StreamArgs<T>& a, const StreamFit& f, int64_t entries, hipStream_t s) {
+  unsigned blocks = (unsigned)entries;
+  if (a.next) {
+    const hipError_t e = persistent_grid(&tucker_pass_kernel<T, NT, JMAX, RB>, NT, f.lds, entries, &blocks);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((tucker_pass_kernel<T, NT, JMAX, RB>), dim3(blocks), dim3(NT), f.lds, s, a);
+  return hipGetLastError();
+}
 
 template <typename T>
-hipError_t launch_finish(const TuckPlan& pl, int threads, int n_agg, int n_dis, int n_theta, int n_phi, int nrhs,
-                         void* F, void* V, hipStream_t s) {
+hipError_t launch_stream(const StreamArgs<T>& a, const StreamFit& f, hipStream_t s) {
+  const int64_t entries = (int64_t)a.n_units * a.n_rblk;
+  if (entries > INT32_MAX) return hipErrorInvalidValue;
+  TFMM_STREAM_CASE(64, 4, 1)
+  TFMM_STREAM_CASE(64, 4, 2)
+  TFMM_STREAM_CASE(64, 4, 4)
+  TFMM_STREAM_CASE(64, 8, 1)
+  TFMM_STREAM_CASE(128, 4, 1)
+  TFMM_STREAM_CASE(128, 4, 2)
+  TFMM_STREAM_CASE(128, 4, 4)
+  TFMM_STREAM_CASE(128, 8, 1)
+  TFMM_STREAM_CASE(256, 4, 1)
+  TFMM_STREAM_CASE(256, 4, 2)
+  TFMM_STREAM_CASE(256, 4, 4)
+  TFMM_STREAM_CASE(256, 8, 1)
+  TFMM_STREAM_CASE(512, 4, 1)
+  TFMM_STREAM_CASE(512, 4, 2)
+  TFMM_STREAM_CASE(512, 4, 4)
+  TFMM_STREAM_CASE(512, 8, 1)
+  TFMM_STREAM_CASE(512, 16, 1)
+  return hipErrorInvalidValue;
+}
+
+template <typename T>
+hipError_t launch_finish(const TuckPlan& pl, int n_agg, int n_dis, int n_theta, int n_phi, int nrhs, void* F, void* V,
+                         hipStream_t s) {
   using C = typename Tr<T>::c;
   if (n_agg + n_dis == 0) return hipSuccess;
-  const size_t lds = n_agg ? Lds<T>(pl.mx).agg_bytes() : 0;
+  const bool staged = pl.mx.stage && FinishLds<T>(pl.mx, true).bytes() <= (size_t)pl.mx.lds;
+  const size_t lds = n_agg ? FinishLds<T>(pl.mx, staged).bytes() : 0;
   // n_dis > 0 with n_agg == 0 runs the disaggregation blocks only: splits from 0
-  const TuckSplit* sp = pl.splits;
-  TFMM_NT_SWITCH(threads,
-                 hipLaunchKernelGGL((tucker_finish_kernel<T, NT>), dim3(n_agg + n_dis, nrhs), dim3(NT), lds, s,
-                                    static_cast<const C*>(pl.factors), pl.items, sp, n_agg, pl.mx, n_theta, n_phi,
-                                    nrhs, static_cast<const C*>(pl.part), pl.part_stride, static_cast<C*>(F),
-                                    static_cast<C*>(V)))
+  hipLaunchKernelGGL(tucker_finish_kernel<T>, dim3(n_agg + n_dis, nrhs), dim3(kFinishThreads), lds, s,
+                     static_cast<const C*>(pl.factors), pl.items, pl.splits, n_agg, pl.mx, staged ? 1 : 0, n_theta,
+                     n_phi, nrhs, static_cast<const C*>(pl.part), pl.part_stride, static_cast<C*>(F),
+                     static_cast<C*>(V));
   return hipGetLastError();
+}
+
+// Either stage (x or G nullptr) or both.
+template <typename T>
+hipError_t launch_units(const TuckPlan& pl, int threads, int n_theta, int n_phi, int nrhs, const void* x, void* F,
+                        const void* G, void* V, bool persistent, hipStream_t s) {
+  using C = typename Tr<T>::c;
+  if (threads != 64 && threads != 128 && threads != 256 && threads != 512) return hipErrorInvalidValue;
+  if (pl.n_splits > 0 && pl.part == nullptr) return hipErrorInvalidValue;
+  if (persistent && pl.next == nullptr) return hipErrorInvalidValue;
+  hipError_t e = hipSuccess;
+  if (V && (e = zero(static_cast<C*>(V), pl.n_basis * nrhs, s, persistent ? pl.next : nullptr)) != hipSuccess) return e;
+  if (pl.n_units == 0) return hipSuccess;
+  StreamFit f;
+  // a layout that fits one of the calls in full takes it in all of them, so that a pass
+  // equals its stages
+  if (stream_fits<T>(pl.mx, threads, nrhs, true, &f)) {
+    if (!G) stream_fits<T>(pl.mx, threads, nrhs, false, &f);
+    StreamArgs<T> a;
+    a.fac = static_cast<const C*>(pl.factors);
+    a.work = pl.work;
+    a.splits = pl.splits;
+    a.n_units = pl.n_units;
+    a.n_theta = n_theta;
+    a.n_phi = n_phi;
+    a.nrhs = nrhs;
+    a.n_rblk = (nrhs + f.rb - 1) / f.rb;
+    a.rstep = (nrhs + a.n_rblk - 1) / a.n_rblk;
+    a.mx = pl.mx;
+    a.staged = f.staged;
+    a.x = static_cast<const C*>(x);
+    a.F = static_cast<C*>(F);
+    a.G = static_cast<const C*>(G);
+    a.V = static_cast<C*>(V);
+    a.part = static_cast<C*>(pl.part);
+    a.part_stride = pl.part_stride;
+    a.next = persistent ? pl.next : nullptr;
+    e = launch_stream<T>(a, f, s);
+  } else {
+    if (x)
+      hipLaunchKernelGGL((tucker_agg_kernel<T, kGenThreads>), dim3(pl.n_units, nrhs), dim3(kGenThreads),
+                         Lds<T>(pl.mx).agg_bytes(), s, static_cast<const C*>(pl.factors), pl.work, pl.splits, pl.mx, n_theta, n_phi, nrhs, static_cast<const C*>(x), static_cast<C*>(F),
+                         static_cast<C*>(pl.part), pl.part_stride);
+    if (G)
+      hipLaunchKernelGGL((tucker_dis_kernel<T, kGenThreads>), dim3(pl.n_units, nrhs), dim3(kGenThreads),
+                         Lds<T>(pl.mx).dis_bytes(), s, static_cast<const C*>(pl.factors), pl.work, pl.splits, pl.mx, n_theta, n_phi, nrhs, static_cast<const C*>(G), static_cast<C*>(V),
+                         static_cast<C*>(pl.part), pl.part_stride);
+    e = hipGetLastError();
+  }
+  if (e != hipSuccess) return e;
+  return launch_finish<T>(pl, x ? pl.n_splits : 0, G ? pl.n_splits : 0, n_theta, n_phi, nrhs, F, V, s);
 }
 
 template <typename T>
 hipError_t launch_tucker_agg(const TuckPlan& pl, int threads, int n_theta, int n_phi, int nrhs, const void* x,
                              void* F, hipStream_t s) {
-  using C = typename Tr<T>::c;
-  if (pl.n_units == 0) return hipSuccess;
-  if (pl.n_splits > 0 && pl.part == nullptr) return hipErrorInvalidValue;
-  TFMM_NT_SWITCH(threads,
-                 hipLaunchKernelGGL((tucker_agg_kernel<T, NT>), dim3(pl.n_units, nrhs), dim3(NT),
-                                    Lds<T>(pl.mx).agg_bytes(), s, static_cast<const C*>(pl.factors), pl.items,
-                                    pl.units, pl.splits, pl.order, pl.mx, n_theta, n_phi, nrhs,
-                                    static_cast<const C*>(x), static_cast<C*>(F), static_cast<C*>(pl.part),
-                                    pl.part_stride))
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_finish<T>(pl, threads, pl.n_splits, 0, n_theta, n_phi, nrhs, F, nullptr, s);
+  return launch_units<T>(pl, threads, n_theta, n_phi, nrhs, x, F, nullptr, nullptr, false, s);
 }
 
 template <typename T>
 hipError_t launch_tucker_disagg(const TuckPlan& pl, int threads, int n_theta, int n_phi, int nrhs, const void* G,
                                 void* V, hipStream_t s) {
-  using C = typename Tr<T>::c;
-  if (threads != 64 && threads != 128 && threads != 256 && threads != 512) return hipErrorInvalidValue;
-  if (pl.n_splits > 0 && pl.part == nullptr) return hipErrorInvalidValue;
-  hipError_t e = zero(static_cast<C*>(V), pl.n_basis * nrhs, s);
-  if (e != hipSuccess || pl.n_units == 0) return e;
-  TFMM_NT_SWITCH(threads,
-                 hipLaunchKernelGGL((tucker_dis_kernel<T, NT>), dim3(pl.n_units, nrhs), dim3(NT),
-                                    Lds<T>(pl.mx).dis_bytes(), s, static_cast<const C*>(pl.factors), pl.items,
-                                    pl.units, pl.splits, pl.order, pl.mx, n_theta, n_phi, nrhs,
-                                    static_cast<const C*>(G), static_cast<C*>(V), static_cast<C*>(pl.part),
-                                    pl.part_stride))
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_finish<T>(pl, threads, 0, pl.n_splits, n_theta, n_phi, nrhs, nullptr, V, s);
+  return launch_units<T>(pl, threads, n_theta, n_phi, nrhs, nullptr, nullptr, G, V, false, s);
 }
 
 template <typename T>
 hipError_t launch_tucker_pass(const TuckPlan& pl, int threads, int n_theta, int n_phi, int nrhs, const void* x,
                               void* F, const void* G, void* V, hipStream_t s) {
-  using C = typename Tr<T>::c;
-  if (threads != 64 && threads != 128 && threads != 256 && threads != 512) return hipErrorInvalidValue;
-  if (pl.n_splits > 0 && pl.part == nullptr) return hipErrorInvalidValue;
-  if (pl.next == nullptr) return hipErrorInvalidValue;
-  hipError_t e = zero(static_cast<C*>(V), pl.n_basis * nrhs, s, pl.next);
-  if (e != hipSuccess || pl.n_units == 0) return e;
-  const int n_list = 2 * pl.n_units;
-  const size_t lds = Lds<T>(pl.mx).bytes();
-  unsigned blocks = 0;
-  TFMM_NT_SWITCH(threads, e = persistent_grid(&tucker_pass_kernel<T, NT>, NT, lds, (int64_t)n_list * nrhs, &blocks))
-  if (e != hipSuccess) return e;
-  TFMM_NT_SWITCH(threads,
-                 hipLaunchKernelGGL((tucker_pass_kernel<T, NT>), dim3(blocks), dim3(NT), lds, s,
-                                    static_cast<const C*>(pl.factors), pl.items, pl.units, pl.splits, pl.pass_list,
-                                    n_list, pl.mx, n_theta, n_phi, nrhs, static_cast<const C*>(x),
-                                    static_cast<C*>(F), static_cast<const C*>(G), static_cast<C*>(V),
-                                    static_cast<C*>(pl.part), pl.part_stride, pl.next))
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_finish<T>(pl, threads, pl.n_splits, pl.n_splits, n_theta, n_phi, nrhs, F, V, s);
+  return launch_units<T>(pl, threads, n_theta, n_phi, nrhs, x, F, G, V, true, s);
 }
 
-template size_t tucker_lds_bytes<float>(const TuckMax&);
-template size_t tucker_lds_bytes<double>(const TuckMax&);
-template hipError_t launch_tucker_agg<float>(const TuckPlan&, int, int, int, int, const void*, void*, hipStream_t);
-template hipError_t launch_tucker_agg<double>(const TuckPlan&, int, int, int, int, const void*, void*, hipStream_t);
-template hipError_t launch_tucker_disagg<float>(const TuckPlan&, int, int, int, int, const void*, void*, hipStream_t);
-template hipError_t launch_tucker_disagg<double>(const TuckPlan&, int, int, int, int, const void*, void*,
-                                                 hipStream_t);
-template hipError_t launch_tucker_pass<float>(const TuckPlan&, int, int, int, int, const void*, void*, const void*,
-                                              void*, hipStream_t);
-template hipError_t launch_tucker_pass<double>(const TuckPlan&, int, int, int, int, const void*, void*, const void*,
-                                               void*, hipStream_t);
+template size_t tucker_lds_bytes<Real>(const TuckMax&);
+template bool stream_fits<Real>(const TuckMax&, int, int, bool, StreamFit*);
+template hipError_t launch_tucker_agg<Real>(const TuckPlan&, int, int, int, int, const void*, void*, hipStream_t);
+template hipError_t launch_tucker_disagg<Real>(const TuckPlan&, int, int, int, int, const void*, void*, hipStream_t);
+template hipError_t launch_tucker_pass<Real>(const TuckPlan&, int, int, int, int, const void*, void*, const void*,
+                                             void*, hipStream_t);
 
 }  // namespace tuckfmm
