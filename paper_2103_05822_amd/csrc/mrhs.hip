@@ -268,6 +268,38 @@ __device__ __forceinline__ void mma_f32(const LdsF32& L, int w, int lane, floatx
   }
 }
 
+// The same step with the wavefronts split over the columns: wavefront w computes the MB
+// 16-row blocks of the tile's first 16 MB rows for its own 16 complex columns (two blocks
+// of 16 real columns, acc[rb][u]).  An element's products and their order are those of
+// mma_f32.
+template <int MB>
+__device__ __forceinline__ void mma_f32_cols(const LdsF32& L, int w, int lane, floatx4 (&acc)[MB][2]) {
+  const int mi = lane % 16, kb = lane / 16;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    float2 b0[2], b1[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int col = 16 * (2 * w + u) + mi;
+      b0[u] = L.b[(8 * h + 2 * kb) * kXS + col];
+      b1[u] = L.b[(8 * h + 2 * kb + 1) * kXS + col];
+    }
+#pragma unroll
+    for (int rb = 0; rb < MB; ++rb) {
+      const float2* pa = &L.a[(16 * rb + mi) * kAS + 8 * h + 2 * kb];
+      const float2 a0 = pa[0], a1 = pa[1];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) acc[rb][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.x, b0[u].x, acc[rb][u], 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) acc[rb][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.y, b0[u].y, acc[rb][u], 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) acc[rb][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.x, b1[u].x, acc[rb][u], 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) acc[rb][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.y, b1[u].y, acc[rb][u], 0, 0, 0);
+    }
+  }
+}
+
 // ------------------------------------------------------------------- FP64 variant
 // The FP32 layout with double2 values (52 KB of LDS).  v_mfma_f64_16x16x4_f64 takes
 // its operands in the lane layout of the FP32 instruction (A row l % 16, B column
@@ -322,6 +354,38 @@ __device__ __forceinline__ void mma_f64(const LdsF64& L, int w, int lane, double
       for (int u = 0; u < kG; ++u) acc[t0 + u] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[2], b1[u].x, acc[t0 + u], 0, 0, 0);
 #pragma unroll
       for (int u = 0; u < kG; ++u) acc[t0 + u] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[3], b1[u].y, acc[t0 + u], 0, 0, 0);
+    }
+  }
+}
+
+// The same step with the wavefronts split over the columns: wavefront w computes the MB
+// 16-row blocks of the tile's first 16 MB rows for its own 16 complex columns (two blocks
+// of 16 real columns, acc[rb][u]).  An element's products and their order are those of
+// mma_f64.
+template <int MB>
+__device__ __forceinline__ void mma_f64_cols(const LdsF64& L, int w, int lane, doublex4 (&acc)[MB][2]) {
+  const int mi = lane % 16, kb = lane / 16;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    double2 b0[2], b1[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int col = 16 * (2 * w + u) + mi;
+      b0[u] = L.b[(8 * h + 2 * kb) * kXS + col];
+      b1[u] = L.b[(8 * h + 2 * kb + 1) * kXS + col];
+    }
+#pragma unroll
+    for (int rb = 0; rb < MB; ++rb) {
+      const double2* pa = &L.a[(16 * rb + mi) * kAS + 8 * h + 2 * kb];
+      const double2 a0 = pa[0], a1 = pa[1];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) acc[rb][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0.x, b0[u].x, acc[rb][u], 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) acc[rb][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0.y, b0[u].y, acc[rb][u], 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) acc[rb][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1.x, b1[u].x, acc[rb][u], 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) acc[rb][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1.y, b1[u].y, acc[rb][u], 0, 0, 0);
     }
   }
 }
@@ -450,12 +514,39 @@ __device__ __forceinline__ void mma_bf16(const LdsBf16<NP>& L, int w, int lane, 
   }
 }
 
+// The same step with the wavefronts split over the columns: NRB blocks of 8 complex rows
+// from the tile's first row for the 16 complex columns of wavefront w.
+template <int NP, int NRB>
+__device__ __forceinline__ void mma_bf16_cols(const LdsBf16<NP>& L, int w, int lane, floatx4 (&acc)[NRB][1]) {
+  const int mi = lane % 16, kb = lane / 16;
+  const uint32_t rot = (mi & 1) ? 16u : 0u;
+  const uint32_t flip = (mi & 1) ? 0u : 0x80000000u;
+  bf16x8 bp[NP];
+#pragma unroll
+  for (int u = 0; u < NP; ++u)
+    bp[u] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(&L.b[u][(16 * w + mi) * kWS + 4 * kb]));
+#pragma unroll
+  for (int rb = 0; rb < NRB; ++rb) {
+    bf16x8 ap[NP];
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      uint4 v = *reinterpret_cast<const uint4*>(&L.a[u][(8 * rb + mi / 2) * kWS + 4 * kb]);
+      v.x = __builtin_rotateright32(v.x, rot) ^ flip;
+      v.y = __builtin_rotateright32(v.y, rot) ^ flip;
+      v.z = __builtin_rotateright32(v.z, rot) ^ flip;
+      v.w = __builtin_rotateright32(v.w, rot) ^ flip;
+      ap[u] = __builtin_bit_cast(bf16x8, v);
+    }
+    mma_pair<NP>(ap, bp, acc[rb][0]);
+  }
+}
+
 // Accumulator register i of lane (ni, g) in block (rb, t) holds real row 4g + i of the
-// block: complex row 16w + 8rb + 2g + i / 2, real part for even i, imaginary for odd,
-// of complex column 16t + ni.  Every lane thus holds whole complex values.
-template <int NTB>
-__device__ __forceinline__ void epilogue_b16(const CGemm& p, float2* Cp, int m0, int n0, int w, int lane,
-                                             const floatx4 (&acc)[2][NTB]) {
+// block: complex row m0 + 8rb + 2g + i / 2, real part for even i, imaginary for odd,
+// of complex column n0 + 16t + ni.  Every lane thus holds whole complex values.
+template <int NRB, int NTB>
+__device__ __forceinline__ void epilogue_b16(const CGemm& p, float2* Cp, int m0, int n0, int lane,
+                                             const floatx4 (&acc)[NRB][NTB]) {
   const int ni = lane % 16, g = lane / 16;
   const bool conj_out = p.flags & kConjC, atomic = p.flags & kAtomicC;
 #pragma unroll
@@ -464,10 +555,10 @@ __device__ __forceinline__ void epilogue_b16(const CGemm& p, float2* Cp, int m0,
     if (n >= p.N) continue;
     const int64_t coff = p.c + col_off(n, p.c_ni, p.c_shi);
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+    for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const int m = m0 + 16 * w + 8 * rb + 2 * g + i;
+        const int m = m0 + 8 * rb + 2 * g + i;
         if (m >= p.M) continue;
         float2 c = make_float2(acc[rb][t][2 * i], acc[rb][t][2 * i + 1]);
         if (conj_out) c.y = -c.y;
@@ -489,7 +580,7 @@ __device__ __forceinline__ void epilogue_b16(const CGemm& p, float2* Cp, int m0,
 // one exchange the even lane owns the rows of registers 0, 1 and the odd lane those
 // of registers 2, 3 as complex values.
 template <typename C2, typename ACC, int NTE>
-__device__ __forceinline__ void epilogue(const CGemm& p, C2* Cp, int m0, int n0, int w, int lane,
+__device__ __forceinline__ void epilogue(const CGemm& p, C2* Cp, int m0, int n0, int lane,
                                          const ACC (&acc)[NTE]) {
   using R = decltype(C2{}.x);
   constexpr bool kF64 = sizeof(R) == 8;
@@ -515,7 +606,7 @@ __device__ __forceinline__ void epilogue(const CGemm& p, C2* Cp, int m0, int n0,
     const int reg0 = odd ? 2 : 0;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int m = m0 + 16 * w + (kF64 ? 4 * (reg0 + i) + g : 4 * g + reg0 + i);
+      const int m = m0 + (kF64 ? 4 * (reg0 + i) + g : 4 * g + reg0 + i);
       if (m >= p.M) continue;
       C2* dst = Cp + coff + (int64_t)m * p.ldc_m;
       const C2 c = i ? c1 : c0;
@@ -590,16 +681,47 @@ __device__ __forceinline__ void store_step(const CGemm& p, bool full, const Stag
     store_stage<VARIANT, false>(p, st, L, tid, ca, cb);
 }
 
-template <int VARIANT, int NTE>
-__device__ __forceinline__ void mma_stage(const typename VarOf<VARIANT>::lds& L, int w, int lane,
-                                          typename VarOf<VARIANT>::acc (&acc)[NTE]) {
-  if constexpr (VARIANT == 0)
-    mma_f32<NTE>(L, w, lane, acc);
-  else if constexpr (VARIANT == 3)
-    mma_f64<NTE>(L, w, lane, acc);
-  else
-    mma_bf16<VARIANT + 1, NTE>(L, w, lane, acc);
-}
+// A wavefront's part of a tile.  Row split: rows 16w .. 16w + 15 and the first NTE
+// 16-column accumulators.  Column split (MB > 0): the first MB 16-row blocks and complex
+// columns 16w .. 16w + 15.
+template <int VARIANT, int MB, int NTE>
+struct Part {
+  static constexpr bool kBf16 = VARIANT == 1 || VARIANT == 2;
+  static constexpr int R = kBf16 ? (MB ? 2 * MB : 2) : (MB ? MB : 1);
+  static constexpr int N = MB ? (kBf16 ? 1 : 2) : NTE;
+  using Acc = typename VarOf<VARIANT>::acc;
+  Acc acc[R][N];
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int n = 0; n < N; ++n) acc[r][n] = Acc{0, 0, 0, 0};
+  }
+  __device__ __forceinline__ void mma(const typename VarOf<VARIANT>::lds& L, int w, int lane) {
+    if constexpr (kBf16 && MB > 0)
+      mma_bf16_cols<VARIANT + 1, R>(L, w, lane, acc);
+    else if constexpr (kBf16)
+      mma_bf16<VARIANT + 1, NTE>(L, w, lane, acc);
+    else if constexpr (VARIANT == 0 && MB > 0)
+      mma_f32_cols<MB>(L, w, lane, acc);
+    else if constexpr (VARIANT == 0)
+      mma_f32<NTE>(L, w, lane, acc[0]);
+    else if constexpr (MB > 0)
+      mma_f64_cols<MB>(L, w, lane, acc);
+    else
+      mma_f64<NTE>(L, w, lane, acc[0]);
+  }
+  __device__ __forceinline__ void store(const CGemm& p, typename VarOf<VARIANT>::c2* Cp, int m0, int n0, int w,
+                                        int lane) const {
+    const int mb = MB ? m0 : m0 + 16 * w, nb = MB ? n0 + 16 * w : n0;
+    if constexpr (kBf16) {
+      epilogue_b16(p, Cp, mb, nb, lane, acc);
+    } else {
+#pragma unroll
+      for (int r = 0; r < R; ++r) epilogue(p, Cp, mb + 16 * r, nb, lane, acc[r]);
+    }
+  }
+};
 
 // One tile: column blocks n0 = tl.n0, tl.n0 + 64, ... below tl.n1, each a full K
 // sweep, walked as one pipeline over (block, K step).  LDS is single buffered: the
@@ -611,20 +733,21 @@ __device__ __forceinline__ void mma_stage(const typename VarOf<VARIANT>::lds& L,
 // active wavefront runs NTE of the eight 16-column accumulators: the products with
 // N = rc columns (the beta and core contractions, most of the work) need only
 // ceil(rc / 8) of them when fewer than 64 right-hand sides share a chunk.
-template <int VARIANT, bool AVEC, bool ACTIVE, int NTE>
+//
+// Tiles of few rows (the angular products, and the last rows of the others) are split over
+// columns instead, so that all four wavefronts, and with them the four SIMDs that a
+// workgroup's wavefronts sit on, share the work: with M = 28 the row split leaves two of
+// them idle.
+template <int VARIANT, bool AVEC, bool ACTIVE, int MB, int NTE>
 __device__ __forceinline__ void run_tile(const CGemm& p, const CTile& tl, const typename VarOf<VARIANT>::c2* A,
                                          const typename VarOf<VARIANT>::c2* B, typename VarOf<VARIANT>::c2* Cp,
                                          typename VarOf<VARIANT>::lds& L) {
   using C2 = typename VarOf<VARIANT>::c2;
-  using ACC = typename VarOf<VARIANT>::acc;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int nsteps = (p.K + kKC - 1) / kKC;
 
-  ACC acc[NTE];
-  if constexpr (ACTIVE) {
-#pragma unroll
-    for (int t = 0; t < NTE; ++t) acc[t] = ACC{0, 0, 0, 0};
-  }
+  Part<VARIANT, MB, NTE> part;
+  if constexpr (ACTIVE) part.clear();
   Walk<C2> wk;
   walk_init(p, A, B, tl.m0, tid, wk);
   walk_block(p, tl.n0, tid, wk);
@@ -647,106 +770,52 @@ __device__ __forceinline__ void run_tile(const CGemm& p, const CTile& tl, const 
         if (ns == 0) walk_block(p, nn0, tid, wk);
         load_step<AVEC>(p, full, ns, wk, st);
       }
-      if constexpr (ACTIVE) mma_stage<VARIANT, NTE>(L, w, lane, acc);
+      if constexpr (ACTIVE) part.mma(L, w, lane);
       if (more) {
         __syncthreads();  // every wavefront is done reading the step
         store_step<VARIANT>(p, full, st, L, tid, ca, cb);
         __syncthreads();
       }
     }
-    if constexpr (ACTIVE) epilogue(p, Cp, tl.m0, n0, w, lane, acc);
+    if constexpr (ACTIVE) part.store(p, Cp, tl.m0, n0, w, lane);
     n0 += kBN;
     if (n0 >= tl.n1) break;
-    if constexpr (ACTIVE) {
-#pragma unroll
-      for (int t = 0; t < NTE; ++t) acc[t] = ACC{0, 0, 0, 0};
-    }
+    if constexpr (ACTIVE) part.clear();
   }
 }
 
-// The wavefront's rows (uniform per wavefront) and the product's width (uniform per
-// workgroup) select the instantiation.
+// The tile's rows and the product's width (uniform per workgroup) select the split and its
+// instantiation: over columns where a wavefront then has fewer accumulators to run (2 per
+// 16 rows, against one per 8 complex columns).  With the row split, a wavefront whose rows
+// lie past the product's M has no matrix-core work.
 template <int VARIANT, bool AVEC>
 __device__ __forceinline__ void run_tile_of(const CGemm& p, const CTile& tl, const typename VarOf<VARIANT>::c2* A,
                                             const typename VarOf<VARIANT>::c2* B, typename VarOf<VARIANT>::c2* Cp,
                                             typename VarOf<VARIANT>::lds& L) {
-  if (tl.m0 + 16 * (int)(threadIdx.x >> 6) >= p.M)
-    run_tile<VARIANT, AVEC, false, 1>(p, tl, A, B, Cp, L);
-  else if (p.N <= 8)
-    run_tile<VARIANT, AVEC, true, 1>(p, tl, A, B, Cp, L);
-  else if (p.N <= 16)
-    run_tile<VARIANT, AVEC, true, 2>(p, tl, A, B, Cp, L);
-  else if (p.N <= 32)
-    run_tile<VARIANT, AVEC, true, 4>(p, tl, A, B, Cp, L);
-  else
-    run_tile<VARIANT, AVEC, true, kNT>(p, tl, A, B, Cp, L);
-}
-
-// The bf16 variants: the pipeline of run_tile with the split at the LDS store.
-template <int VARIANT, bool AVEC, bool ACTIVE, int NTB>
-__device__ __forceinline__ void run_tile_b16(const CGemm& p, const CTile& tl, const float2* A, const float2* B,
-                                              float2* Cp, typename VarOf<VARIANT>::lds& L) {
-  constexpr int NP = VARIANT + 1;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int nsteps = (p.K + kKC - 1) / kKC;
-
-  floatx4 acc[2][NTB];
-  if constexpr (ACTIVE) {
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-      for (int t = 0; t < NTB; ++t) acc[rb][t] = floatx4{0, 0, 0, 0};
+  // accumulators of the row split: one per 8 (FP32, FP64) or 16 (bf16) complex columns
+  constexpr bool kBf16 = VARIANT == 1 || VARIANT == 2;
+  constexpr int kN8 = 1, kN16 = kBf16 ? 1 : 2, kN32 = kBf16 ? 2 : 4, kN64 = kBf16 ? kNB : kNT;
+  const int rows = p.M - tl.m0;
+  if (p.N > 32 && rows <= 48) {
+    if (rows <= 16)
+      run_tile<VARIANT, AVEC, true, 1, 1>(p, tl, A, B, Cp, L);
+    else if (rows <= 32)
+      run_tile<VARIANT, AVEC, true, 2, 1>(p, tl, A, B, Cp, L);
+    else
+      run_tile<VARIANT, AVEC, true, 3, 1>(p, tl, A, B, Cp, L);
+  } else if (p.N > 16 && rows <= 16) {
+    run_tile<VARIANT, AVEC, true, 1, 1>(p, tl, A, B, Cp, L);
+  } else if (16 * (int)(threadIdx.x >> 6) >= rows) {
+    run_tile<VARIANT, AVEC, false, 0, 1>(p, tl, A, B, Cp, L);
+  } else if (p.N <= 8) {
+    run_tile<VARIANT, AVEC, true, 0, kN8>(p, tl, A, B, Cp, L);
+  } else if (p.N <= 16) {
+    run_tile<VARIANT, AVEC, true, 0, kN16>(p, tl, A, B, Cp, L);
+  } else if (p.N <= 32) {
+    run_tile<VARIANT, AVEC, true, 0, kN32>(p, tl, A, B, Cp, L);
+  } else {
+    run_tile<VARIANT, AVEC, true, 0, kN64>(p, tl, A, B, Cp, L);
   }
-  Walk<float2> wk;
-  walk_init(p, A, B, tl.m0, tid, wk);
-  walk_block(p, tl.n0, tid, wk);
-  const uint32_t ca = conj_mask(p, kConjA), cb = conj_mask(p, kConjB);
-  Stage<float2> st;
-  load_step<AVEC>(p, kKC <= p.K, 0, wk, st);
-  store_step<VARIANT>(p, kKC <= p.K, st, L, tid, ca, cb);
-  __syncthreads();
-  for (int n0 = tl.n0;;) {
-    for (int s = 0; s < nsteps; ++s) {
-      int nn0 = n0, ns = s + 1;
-      if (ns == nsteps) {
-        ns = 0;
-        nn0 += kBN;
-      }
-      const bool more = nn0 < tl.n1, full = (ns + 1) * kKC <= p.K;
-      if (more) {
-        if (ns == 0) walk_block(p, nn0, tid, wk);
-        load_step<AVEC>(p, full, ns, wk, st);
-      }
-      if constexpr (ACTIVE) mma_bf16<NP, NTB>(L, w, lane, acc);
-      if (more) {
-        __syncthreads();  // every wavefront is done reading the step
-        store_step<VARIANT>(p, full, st, L, tid, ca, cb);
-        __syncthreads();
-      }
-    }
-    if constexpr (ACTIVE) epilogue_b16<NTB>(p, Cp, tl.m0, n0, w, lane, acc);
-    n0 += kBN;
-    if (n0 >= tl.n1) break;
-    if constexpr (ACTIVE) {
-#pragma unroll
-      for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-        for (int t = 0; t < NTB; ++t) acc[rb][t] = floatx4{0, 0, 0, 0};
-    }
-  }
-}
-
-template <int VARIANT, bool AVEC>
-__device__ __forceinline__ void run_tile_of_b16(const CGemm& p, const CTile& tl, const float2* A, const float2* B,
-                                                 float2* Cp, typename VarOf<VARIANT>::lds& L) {
-  if (tl.m0 + 16 * (int)(threadIdx.x >> 6) >= p.M)
-    run_tile_b16<VARIANT, AVEC, false, 1>(p, tl, A, B, Cp, L);
-  else if (p.N <= 16)
-    run_tile_b16<VARIANT, AVEC, true, 1>(p, tl, A, B, Cp, L);
-  else if (p.N <= 32)
-    run_tile_b16<VARIANT, AVEC, true, 2>(p, tl, A, B, Cp, L);
-  else
-    run_tile_b16<VARIANT, AVEC, true, kNB>(p, tl, A, B, Cp, L);
 }
 
 template <int VARIANT>
@@ -764,9 +833,9 @@ __global__ __launch_bounds__(kMT) __attribute__((amdgpu_waves_per_eu(VarOf<VARIA
   // stride
   if constexpr (VARIANT == 1 || VARIANT == 2) {
     if (p.lda_k == 1 && !((p.a | p.lda_m) & 1))
-      run_tile_of_b16<VARIANT, true>(p, tl, A, B, Cp, L);
+      run_tile_of<VARIANT, true>(p, tl, A, B, Cp, L);
     else
-      run_tile_of_b16<VARIANT, false>(p, tl, A, B, Cp, L);
+      run_tile_of<VARIANT, false>(p, tl, A, B, Cp, L);
   } else if constexpr (VARIANT == 3) {
     run_tile_of<VARIANT, false>(p, tl, A, B, Cp, L);
   } else {
