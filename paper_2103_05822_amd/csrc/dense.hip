@@ -1,13 +1,13 @@
 // Dense (plain-method) aggregation and disaggregation, eqs. (3) and (5), Figs. 2(a)
-// and 3(a).  Both kernels are pure HBM streams over the far-field array
-// [N][2][N_dir] (a group's rows are contiguous):
-//   aggregation    F[g][col] = sum_n A[n][col] x[n]      one thread per column,
-//                                                         rows walked in order
-//   disaggregation V[n] = sum_col conj(A[n][col]) G[g][col]   one wavefront per row,
-//                                                         lane-strided, butterfly sum
-// with up to 8 right-hand sides per read of A.  With 2 or more right-hand sides the
-// disaggregation works on blocks of rows of one group instead (see
-// dense_disagg_block_kernel).
+// and 3(a).  All kernels are pure HBM streams over the far-field array [N][2][N_dir] (a
+// group's rows are contiguous):
+//   aggregation    F[g][col] = sum_n A[n][col] x[n]
+//   disaggregation V[n] = sum_col conj(A[n][col]) G[g][col]
+// With one right-hand side they run on the vector units: the aggregation a column per
+// lane, the disaggregation a row per wavefront.  With more, up to 8 right-hand sides share
+// a read of A and the products run on the matrix cores (16 real columns hold the real and
+// imaginary parts of 8 right-hand sides), which leaves the vector registers to loads in
+// flight.
 #include <hip/hip_runtime.h>
 #include "cplx.hpp"
 #include "kernels.hpp"
@@ -17,76 +17,231 @@ namespace tuckfmm {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kCols = 2;     // columns per thread in aggregation
+constexpr int kWaves = kThreads / 64;
 
-// Right-hand sides are taken RB at a time (blockIdx.y walks the blocks of RB): every
-// element of A read from HBM serves RB right-hand sides, so a pass over R <= 8 of
-// them reads A once.  nr = min(RB, nrhs - r0) of a block's RB columns are valid.
-
-template <typename T, int RB>
+// Aggregation with one right-hand side.  A workgroup takes 64 kCols columns of a group;
+// its four wavefronts take the group's rows in turn and meet in LDS, so that a layout of
+// few groups still fills the chip (24 groups of 909 rows and 5700 columns, complex128: 452 us
+// with a thread per column and all rows in one wavefront, in 288 workgroups, about 310 now).
+template <typename T>
 __global__ __launch_bounds__(kThreads) void dense_agg_kernel(const typename Tr<T>::c* __restrict__ A,
                                                              const DenseGroup* __restrict__ groups, int n_chunks,
-                                                             int ncols, int nrhs,
-                                                             const typename Tr<T>::c* __restrict__ x,
+                                                             int ncols, const typename Tr<T>::c* __restrict__ x,
                                                              typename Tr<T>::c* __restrict__ F) {
   using C = typename Tr<T>::c;
-  // rows per iteration: the x values of a row are uniform across the workgroup and
-  // live in scalar registers, RB of them per row
-  constexpr int kRowUnroll = RB >= 4 ? 2 : 4;
+  constexpr int kCols = 2 * Tr<T>::E;  // columns per lane
+  constexpr int U = 4;                 // rows in flight
+  __shared__ C sum[kWaves - 1][64 * kCols];
   const int g = blockIdx.x / n_chunks;
-  const int chunk = blockIdx.x - g * n_chunks;
-  const int r0 = blockIdx.y * RB;
-  const int nr = min(RB, nrhs - r0);
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int c0 = (blockIdx.x - g * n_chunks) * 64 * kCols + lane;
   const DenseGroup grp = groups[g];
-  const int c0 = chunk * kThreads * kCols + threadIdx.x;
-  bool in[kCols];
+  C acc[kCols];
+  int off[kCols];
 #pragma unroll
-  for (int j = 0; j < kCols; ++j) in[j] = c0 + kThreads * j < ncols;
-  C acc[kCols][RB];
+  for (int j = 0; j < kCols; ++j) {
+    acc[j] = czero<C>();
+    off[j] = min(c0 + 64 * j, ncols - 1);  // (columns past the end are not stored)
+  }
+  const C* base = A + grp.row0 * ncols;
+  const C* xb = x + grp.row0;
+  int n = w;
+  for (; n + kWaves * (U - 1) < grp.nb; n += kWaves * U) {
+    C a[U][kCols];
 #pragma unroll
-  for (int j = 0; j < kCols; ++j)
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-    for (int r = 0; r < RB; ++r) acc[j][r] = czero<C>();
-  const C* base = A + grp.row0 * ncols + c0;
-  const C* xb = x + grp.row0 * nrhs + r0;
-  int n = 0;
-  for (; n + kRowUnroll <= grp.nb; n += kRowUnroll) {
-    C a[kRowUnroll][kCols];
+      for (int j = 0; j < kCols; ++j) a[u][j] = base[(int64_t)(n + kWaves * u) * ncols + off[j]];
 #pragma unroll
-    for (int u = 0; u < kRowUnroll; ++u)
+    for (int u = 0; u < U; ++u) {
+      const C xn = xb[n + kWaves * u];
 #pragma unroll
-      for (int j = 0; j < kCols; ++j)
-        a[u][j] = in[j] ? base[(int64_t)(n + u) * ncols + kThreads * j] : czero<C>();
-#pragma unroll
-    for (int u = 0; u < kRowUnroll; ++u) {
-      C xn[RB];
-#pragma unroll
-      for (int r = 0; r < RB; ++r) xn[r] = r < nr ? xb[(int64_t)(n + u) * nrhs + r] : czero<C>();
-#pragma unroll
-      for (int j = 0; j < kCols; ++j)
-#pragma unroll
-        for (int r = 0; r < RB; ++r) cfma(acc[j][r], a[u][j], xn[r]);
+      for (int j = 0; j < kCols; ++j) cfma(acc[j], a[u][j], xn);
     }
   }
-  for (; n < grp.nb; ++n) {
-    C xn[RB];
+  for (; n < grp.nb; n += kWaves) {
+    const C xn = xb[n];
 #pragma unroll
-    for (int r = 0; r < RB; ++r) xn[r] = r < nr ? xb[(int64_t)n * nrhs + r] : czero<C>();
+    for (int j = 0; j < kCols; ++j) cfma(acc[j], base[(int64_t)n * ncols + off[j]], xn);
+  }
+  if (w > 0) {
 #pragma unroll
-    for (int j = 0; j < kCols; ++j) {
-      const C a = in[j] ? base[(int64_t)n * ncols + kThreads * j] : czero<C>();
+    for (int j = 0; j < kCols; ++j) sum[w - 1][64 * j + lane] = acc[j];
+  }
+  __syncthreads();
+  if (w > 0) return;
 #pragma unroll
-      for (int r = 0; r < RB; ++r) cfma(acc[j][r], a, xn[r]);
+  for (int j = 0; j < kCols; ++j) {
+#pragma unroll
+    for (int v = 0; v < kWaves - 1; ++v) {
+      acc[j].x += sum[v][64 * j + lane].x;
+      acc[j].y += sum[v][64 * j + lane].y;
+    }
+    if (c0 + 64 * j < ncols) F[(int64_t)g * ncols + c0 + 64 * j] = acc[j];
+  }
+}
+
+// ---------------------------------------------------- several right-hand sides
+//
+// FP32 and FP64 matrix instructions of 16 x 16 x 4: lane l feeds row (column) l % 16 and
+// k = l / 16 of A (B); register i of lane l holds column l % 16 of row 4 (l / 16) + i
+// (FP32) or 4 i + l / 16 (FP64).  Column 2 r + q of B is part q (real, imaginary) of
+// right-hand side r, which is how a vector stores its values, so a lane reads one real
+// number and a wavefront whole lines.  A complex product takes two instructions, one for
+// each part of A:
+//   aggregation    Re A [Re x, Im x]  +  Im A [-Im x, Re x]
+//   disaggregation Re A [Re G, Im G]  +  Im A [ Im G, -Re G]   (conj A)
+// whose second operand is the neighbouring lane's value, negated in one parity.  Columns
+// past the last right-hand side read a clamped one and are not stored.  200 groups of 232
+// rows and 2450 columns, complex128, 8 right-hand sides, both stages: 769 us (4.9 TB/s);
+// 940 us with the products on the vector units, whose 64 sums a thread left two wavefronts
+// a SIMD to hide the loads.
+template <typename T>
+struct DenseMfma;
+template <>
+struct DenseMfma<float> {
+  typedef float acc __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ acc mul(float a, float b, acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int i, int g) { return 4 * g + i; }
+};
+template <>
+struct DenseMfma<double> {
+  typedef double acc __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ acc mul(double a, double b, acc c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int i, int g) { return 4 * i + g; }
+};
+
+// The neighbouring lane's value (lane l ^ 1).
+__device__ __forceinline__ uint32_t other_lane(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true);
+}
+__device__ __forceinline__ float other_part(float v) { return __uint_as_float(other_lane(__float_as_uint(v))); }
+__device__ __forceinline__ double other_part(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = other_lane((uint32_t)u), hi = other_lane((uint32_t)(u >> 32));
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Aggregation: a workgroup takes 16 MB columns of a group for up to 8 right-hand sides; its
+// wavefronts take the rows in steps of 4, in turn, and meet in LDS.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void dense_agg_mfma_kernel(const typename Tr<T>::c* __restrict__ A,
+                                                                  const DenseGroup* __restrict__ groups, int n_chunks,
+                                                                  int ncols, int nrhs,
+                                                                  const typename Tr<T>::c* __restrict__ x,
+                                                                  typename Tr<T>::c* __restrict__ F) {
+  using C = typename Tr<T>::c;
+  using Acc = typename DenseMfma<T>::acc;
+  constexpr int MB = 4;
+  constexpr int U = 2;  // steps in flight
+  __shared__ T sum[kWaves - 1][MB][4][64];
+  const int g = blockIdx.x / n_chunks;
+  const int lane = threadIdx.x & 63, li = lane & 15, kg = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int c0 = (blockIdx.x - g * n_chunks) * 16 * MB;
+  const int r0 = blockIdx.y * 8, nr = min(8, nrhs - r0);
+  const DenseGroup grp = groups[g];
+  const int part = min(li, 2 * nr - 1);
+  const C* base = A + grp.row0 * ncols;
+  const T* xb = reinterpret_cast<const T*>(x + grp.row0 * nrhs + r0) + part;
+  int off[MB];
+#pragma unroll
+  for (int m = 0; m < MB; ++m) off[m] = min(c0 + 16 * m + li, ncols - 1);
+  Acc acc[MB];
+#pragma unroll
+  for (int m = 0; m < MB; ++m) acc[m] = Acc{0, 0, 0, 0};
+  for (int n0 = 4 * w; n0 < grp.nb; n0 += 4 * kWaves * U) {
+    C a[U][MB];
+    T b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int n = n0 + 4 * kWaves * u + kg, nc = min(n, grp.nb - 1);
+#pragma unroll
+      for (int m = 0; m < MB; ++m) a[u][m] = base[(int64_t)nc * ncols + off[m]];
+      b[u] = xb[(int64_t)nc * 2 * nrhs];
+      if (n >= grp.nb) {
+        b[u] = T(0);
+#pragma unroll
+        for (int m = 0; m < MB; ++m) a[u][m] = czero<C>();
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const T o = other_part(b[u]), b2 = li & 1 ? o : -o;
+#pragma unroll
+      for (int m = 0; m < MB; ++m) acc[m] = DenseMfma<T>::mul(a[u][m].x, b[u], acc[m]);
+#pragma unroll
+      for (int m = 0; m < MB; ++m) acc[m] = DenseMfma<T>::mul(a[u][m].y, b2, acc[m]);
     }
   }
+  if (w > 0) {
 #pragma unroll
-  for (int j = 0; j < kCols; ++j)
-    if (in[j]) {
-      C* out = F + ((int64_t)g * ncols + c0 + kThreads * j) * nrhs + r0;
+    for (int m = 0; m < MB; ++m)
 #pragma unroll
-      for (int r = 0; r < RB; ++r)
-        if (r < nr) out[r] = acc[j][r];
+      for (int i = 0; i < 4; ++i) sum[w - 1][m][i][lane] = acc[m][i];
+  }
+  __syncthreads();
+  if (w > 0 || li >= 2 * nr) return;
+#pragma unroll
+  for (int m = 0; m < MB; ++m)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      T v = acc[m][i];
+#pragma unroll
+      for (int k = 0; k < kWaves - 1; ++k) v += sum[k][m][i][lane];
+      const int c = c0 + 16 * m + DenseMfma<T>::row(i, kg);
+      if (c < ncols) reinterpret_cast<T*>(F + ((int64_t)g * ncols + c) * nrhs + r0)[li] = v;
     }
+}
+
+// Disaggregation: a wavefront takes a block of up to 16 rows of one group for up to 8
+// right-hand sides and walks the columns in steps of 4.  The plan orders the blocks so that
+// each XCD works on a few groups at a time, whose G then stays in its L2 (it is read once
+// per block, half the bytes of A's).
+template <typename T>
+__global__ __launch_bounds__(64) void dense_disagg_mfma_kernel(const typename Tr<T>::c* __restrict__ A,
+                                                               const DenseBlock* __restrict__ blocks, int ncols,
+                                                               int nrhs, const typename Tr<T>::c* __restrict__ Gin,
+                                                               typename Tr<T>::c* __restrict__ V) {
+  using C = typename Tr<T>::c;
+  using Acc = typename DenseMfma<T>::acc;
+  constexpr int U = 8;  // steps in flight
+  const int lane = threadIdx.x, li = lane & 15, kg = lane >> 4;
+  const DenseBlock b = blocks[blockIdx.x];
+  const int r0 = blockIdx.y * 8, nr = min(8, nrhs - r0);
+  const C* row = A + (b.row0 + min(li, b.rows - 1)) * ncols;
+  const T* gv = reinterpret_cast<const T*>(Gin + (int64_t)b.group * ncols * nrhs + r0) + min(li, 2 * nr - 1);
+  Acc acc[2] = {Acc{0, 0, 0, 0}, Acc{0, 0, 0, 0}};
+  for (int c0 = 0; c0 < ncols; c0 += 4 * U) {
+    C a[U];
+    T gt[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = c0 + 4 * u + kg, cc = min(c, ncols - 1);
+      a[u] = row[cc];
+      gt[u] = gv[(int64_t)cc * 2 * nrhs];
+      if (c >= ncols) {
+        a[u] = czero<C>();
+        gt[u] = T(0);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const T o = other_part(gt[u]), g2 = li & 1 ? -o : o;
+      acc[0] = DenseMfma<T>::mul(a[u].x, gt[u], acc[0]);
+      acc[1] = DenseMfma<T>::mul(a[u].y, g2, acc[1]);
+    }
+  }
+  if (li >= 2 * nr) return;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int m = DenseMfma<T>::row(i, kg);
+    if (m < b.rows) reinterpret_cast<T*>(V + (b.row0 + m) * nrhs + r0)[li] = acc[0][i] + acc[1][i];
+  }
 }
 
 // Disaggregation with one right-hand side: a wavefront per row, four columns in
@@ -132,141 +287,24 @@ __global__ __launch_bounds__(kThreads) void dense_disagg_kernel(const typename T
   if (lane == 0) V[n] = s;
 }
 
-// Disaggregation with RB = 2, 4 or 8 right-hand sides per read of A, over the row
-// blocks of the plan (up to 16 rows of one group).  Read per row, the group's G would
-// cost RB times the row's bytes, and a lane's RB values of one column sit 16 RB bytes
-// apart from the next lane's, so each load instruction would touch 64 cache lines.
-// Instead the workgroup walks the columns in chunks of 64: its 256 threads load the
-// chunk's G[g][c][r0 .. r0 + RB) with coalesced loads into LDS (double buffered, one
-// barrier per chunk), and wavefront w, owning rows 4w .. 4w + 3 of the block, reads a
-// lane's column from there for its four rows while the rows of A stream from HBM
-// (prefetched one chunk ahead).  The plan orders the blocks so that each XCD works on
-// a few groups at a time, whose G then stays in its L2.
-template <typename T, int RB>
-__global__ __launch_bounds__(kThreads) void dense_disagg_block_kernel(const typename Tr<T>::c* __restrict__ A,
-                                                                      const DenseBlock* __restrict__ blocks,
-                                                                      int ncols, int nrhs,
-                                                                      const typename Tr<T>::c* __restrict__ Gin,
-                                                                      typename Tr<T>::c* __restrict__ V) {
-  using C = typename Tr<T>::c;
-  constexpr int RW = 4;                               // rows per wavefront
-  constexpr int CW = 64;                              // columns per chunk
-  constexpr int GS = RB + 1;                          // LDS row stride (complex): spreads the banks
-  constexpr int GL = (CW * RB + kThreads - 1) / kThreads;  // G elements per thread and chunk
-  __shared__ C gsh[2][CW * GS];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const DenseBlock b = blocks[blockIdx.x];
-  const int i0 = RW * w;
-  const int nrow = max(0, min(RW, b.rows - i0));  // uniform per wavefront; 0: loads and barriers only
-  const int r0 = blockIdx.y * RB;
-  const int nr = min(RB, nrhs - r0);
-  const C* rows = A + (b.row0 + min(i0, b.rows - 1)) * ncols;
-  const C* gv = Gin + (int64_t)b.group * ncols * nrhs + r0;
-  const int nchunks = (ncols + CW - 1) / CW;
-
-  C greg[GL];
-  auto load_g = [&](int chunk) {
-#pragma unroll
-    for (int k = 0; k < GL; ++k) {
-      const int e = tid + kThreads * k, cc = e / RB, r = e % RB, c = chunk * CW + cc;
-      greg[k] = e < CW * RB && c < ncols && r < nr ? gv[(int64_t)c * nrhs + r] : czero<C>();
-    }
-  };
-  auto store_g = [&](int buf) {
-#pragma unroll
-    for (int k = 0; k < GL; ++k) {
-      const int e = tid + kThreads * k;
-      if (e < CW * RB) gsh[buf][(e / RB) * GS + e % RB] = greg[k];
-    }
-  };
-  auto load_a = [&](int chunk, C (&a)[RW]) {
-    const int c = chunk * CW + lane;
-#pragma unroll
-    for (int i = 0; i < RW; ++i) a[i] = i < nrow && c < ncols ? rows[(int64_t)i * ncols + c] : czero<C>();
-  };
-
-  C acc[RW][RB];
-#pragma unroll
-  for (int i = 0; i < RW; ++i)
-#pragma unroll
-    for (int r = 0; r < RB; ++r) acc[i][r] = czero<C>();
-  C a[RW], an[RW];
-  load_g(0);
-  load_a(0, a);
-  store_g(0);
-  __syncthreads();
-  for (int chunk = 0; chunk < nchunks; ++chunk) {
-    const bool more = chunk + 1 < nchunks;
-    if (more) {
-      load_a(chunk + 1, an);
-      load_g(chunk + 1);
-    }
-    const C* gc = &gsh[chunk & 1][lane * GS];
-    C gt[RB];
-#pragma unroll
-    for (int r = 0; r < RB; ++r) gt[r] = gc[r];
-#pragma unroll
-    for (int i = 0; i < RW; ++i)
-#pragma unroll
-      for (int r = 0; r < RB; ++r) cfma_conj(acc[i][r], a[i], gt[r]);
-    if (more) {
-      store_g((chunk + 1) & 1);  // that buffer was last read before the previous barrier
-#pragma unroll
-      for (int i = 0; i < RW; ++i) a[i] = an[i];
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < RW; ++i) {
-    if (i >= nrow) break;
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      const C sum = wave_sum(acc[i][r]);
-      if (lane == 0 && r < nr) V[(b.row0 + i0 + i) * nrhs + r0 + r] = sum;
-    }
-  }
-}
-
-// RB for a call: the smallest of 1, 2, 4, 8 covering nrhs (8 beyond).
-int rhs_block(int nrhs) { return nrhs >= 8 ? 8 : (nrhs > 2 ? 4 : nrhs); }
-
 }  // namespace
-
-#define TFMM_RB_SWITCH(rb, ...) \
-  switch (rb) {                  \
-    case 1: {                    \
-      constexpr int RB = 1;      \
-      __VA_ARGS__;               \
-      break;                     \
-    }                            \
-    case 2: {                    \
-      constexpr int RB = 2;      \
-      __VA_ARGS__;               \
-      break;                     \
-    }                            \
-    case 4: {                    \
-      constexpr int RB = 4;      \
-      __VA_ARGS__;               \
-      break;                     \
-    }                            \
-    default: {                   \
-      constexpr int RB = 8;      \
-      __VA_ARGS__;               \
-      break;                     \
-    }                            \
-  }
 
 template <typename T>
 hipError_t launch_dense_agg(const void* A, const DenseGroup* groups, int n_groups, int ncols, int nrhs,
                             const void* x, void* F, hipStream_t s) {
   using C = typename Tr<T>::c;
   if (n_groups == 0) return hipSuccess;
-  const int n_chunks = (ncols + kThreads * kCols - 1) / (kThreads * kCols);
-  const int rb = rhs_block(nrhs);
-  dim3 grid((unsigned)n_groups * n_chunks, (nrhs + rb - 1) / rb);
-  TFMM_RB_SWITCH(rb, hipLaunchKernelGGL((dense_agg_kernel<T, RB>), grid, dim3(kThreads), 0, s,
-                                        static_cast<const C*>(A), groups, n_chunks, ncols, nrhs,
-                                        static_cast<const C*>(x), static_cast<C*>(F)))
+  if (nrhs == 1) {
+    const int n_chunks = (ncols + 128 * Tr<T>::E - 1) / (128 * Tr<T>::E);
+    hipLaunchKernelGGL(dense_agg_kernel<T>, dim3((unsigned)n_groups * n_chunks), dim3(kThreads), 0, s,
+                       static_cast<const C*>(A), groups, n_chunks, ncols, static_cast<const C*>(x),
+                       static_cast<C*>(F));
+  } else {
+    const int n_chunks = (ncols + 63) / 64;
+    hipLaunchKernelGGL(dense_agg_mfma_kernel<T>, dim3((unsigned)n_groups * n_chunks, (nrhs + 7) / 8), dim3(kThreads),
+                       0, s, static_cast<const C*>(A), groups, n_chunks, ncols, nrhs, static_cast<const C*>(x),
+                       static_cast<C*>(F));
+  }
   return hipGetLastError();
 }
 
@@ -276,19 +314,16 @@ hipError_t launch_dense_disagg(const void* A, const int64_t* offsets, int n_grou
                                void* V, hipStream_t s) {
   using C = typename Tr<T>::c;
   if (n_rows == 0) return hipSuccess;
-  const int rb = rhs_block(nrhs);
-  if (rb == 1) {
-    const int64_t blocks = (n_rows + kThreads / 64 - 1) / (kThreads / 64);
+  if (nrhs == 1) {
+    const int64_t blocks = (n_rows + kWaves - 1) / kWaves;
     hipLaunchKernelGGL((dense_disagg_kernel<T>), dim3((unsigned)blocks), dim3(kThreads), 0, s,
                        static_cast<const C*>(A), offsets, n_groups, n_rows, ncols, static_cast<const C*>(G),
                        static_cast<C*>(V));
     return hipGetLastError();
   }
   if (n_blocks <= 0 || row_blocks == nullptr) return hipErrorInvalidValue;
-  dim3 grid((unsigned)n_blocks, (nrhs + rb - 1) / rb);
-  TFMM_RB_SWITCH(rb, hipLaunchKernelGGL((dense_disagg_block_kernel<T, RB>), grid, dim3(kThreads), 0, s,
-                                        static_cast<const C*>(A), row_blocks, ncols, nrhs,
-                                        static_cast<const C*>(G), static_cast<C*>(V)))
+  hipLaunchKernelGGL((dense_disagg_mfma_kernel<T>), dim3((unsigned)n_blocks, (nrhs + 7) / 8), dim3(64), 0, s,
+                     static_cast<const C*>(A), row_blocks, ncols, nrhs, static_cast<const C*>(G), static_cast<C*>(V));
   return hipGetLastError();
 }
 
