@@ -306,7 +306,7 @@ fmm_status lds_check(size_t bytes) {
 struct Route {
   bool mfma = false;  // matrix-core products (else the streaming kernels)
   int variant = 0;    // grouped GEMM arithmetic: 0 FP32, 1 BF16x2, 2 BF16x3, 3 FP64
-  int tile_steps = 0, rhs_chunk = 0, order = 0;
+  int tile_steps = 0, rhs_chunk = 0, order = kMrhsUntunedOrder;
   int threads = 512;  // streaming kernels' workgroup size
 };
 

@@ -66,7 +66,7 @@ struct MrhsPlan {
   int nrhs = 0;
   int rhs_chunk = 0;   // columns per chunk
   int tile_steps = 0;  // K steps a workgroup aims to run (column blocks per tile)
-  int order = 0;       // angular contraction order: 0 each item's cheaper, 1 theta first, 2 phi first
+  int order = 0;       // angular contraction order: 0 each item's cheaper, 1 theta first, 2 phi first, 3 untuned
   char* dev = nullptr;  // one allocation: problem tables, tile lists, scratch
   size_t dev_bytes = 0;
   char* scratch = nullptr;
@@ -100,7 +100,10 @@ struct PrecSlot {
 
 // Multi-RHS path (mrhs_plan.cpp).
 constexpr int kMrhsDefaultSteps = 16;
+constexpr int kMrhsFewSteps = 8;     // the same for layouts of at most kMrhsFewItems items
+constexpr size_t kMrhsFewItems = 64;
 constexpr int kMrhsDefaultChunk = 64;
+constexpr int kMrhsUntunedOrder = 3;  // angular order of untuned calls (see mrhs_build_host)
 // Host image of the tables: problems [8][n_items] (product j of item i at j n_items + i)
 // and tile lists [agg, dis, pass][launch] per chunk; scratch offsets in complex elements.
 struct MrhsHostChunk {
