@@ -327,6 +327,7 @@ def main():
     tucker_ms = ms["tucker_pass_f32"]
     tucker_gbs = gbs["tucker_pass_f32"]
     dom = "tucker_pass_f32"
+    roof_bytes = per_stage_bytes[dom] - fac32
 
     result = {
         "metric": "agg+disagg pass time & GB/s: Tucker FP32 vs dense FP64, 1 GPU, at <=1e-5 rel err",
@@ -347,11 +348,14 @@ def main():
         "stage_ms": {k: round(v, 4) for k, v in ms.items()},
         "first_launch_ms": first_ms,
         "stage_GBps": {k: round(v, 1) for k, v in gbs.items()},
-        "roofline": {"bound": "hbm", "kernel": "tucker_pass_kernel<float> (+ V zeroing)", "achieved": round(gbs[dom], 1),
+        # the pass kernel reads the factors once for both stages: its roofline counts them
+        # once, `value` once per stage (the work of the two calls it replaces)
+        "roofline": {"bound": "hbm", "kernel": "tucker_pass_kernel<float> (+ V zeroing)",
+                     "achieved": round(roof_bytes / (ms[dom] * 1e-3) / 1e9, 1),
                      "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": round(gbs[dom] / HBM_PEAK_GBS, 4),
+                     "unit": "GB/s", "frac": round(roof_bytes / (ms[dom] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                      "traffic": measured_traffic("tucker_pass_kernel<float>", "tucker.hip", w.name),
-                     "bytes_per_launch": per_stage_bytes[dom]},
+                     "bytes_per_launch": roof_bytes},
         "copy_GBps": round(copy_gbs, 1),
         "memory_MB": {"tucker_factors_f32": round(fac32 / 2 ** 20, 1),
                       "dense_f64": round(2 * N * nd * 16 / 2 ** 20, 1)},
@@ -483,8 +487,8 @@ def fp64_pass(T, torch, h, lay, w, ranks, x64, g64, sample, dense_ms):
     V = torch.empty(N, dtype=torch.complex128, device="cuda")
     ms = graph_time(torch, T, h, T.FMM_C128, 1, x64, F, g64, V)
     b_stage, fac = tucker_stage_bytes(ranks, lay.offsets, w.n_theta, w.n_phi, 16)
-    gbs = 2 * b_stage / (ms * 1e-3) / 1e9
-    rep = {"pass_ms": round(ms, 4), "GBps": round(gbs, 1), "hbm_frac": round(gbs / HBM_PEAK_GBS, 4),
+    gbs = 2 * b_stage / (ms * 1e-3) / 1e9  # factors once per stage; hbm_frac: once
+    rep = {"pass_ms": round(ms, 4), "GBps": round(gbs, 1), "hbm_frac": round((2 * b_stage - fac) / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
            "factors_MB_f64": round(fac / 2 ** 20, 1)}
     if dense_ms:
         rep["speedup_vs_dense_f64_pass"] = round(dense_ms / ms, 2)
@@ -549,10 +553,10 @@ def gamma_pass(args, T, torch, lay, dense, w, gamma, x32, g32, sample, dense_ms)
         V = torch.empty(N, dtype=torch.complex64, device="cuda")
         ms = graph_time(torch, T, h2, T.FMM_C64, 1, x32, F, g32, V)
         b_stage, fac = tucker_stage_bytes(ranks, lay.offsets, w.n_theta, w.n_phi, 8)
-        gbs = 2 * b_stage / (ms * 1e-3) / 1e9
+        gbs = 2 * b_stage / (ms * 1e-3) / 1e9  # factors once per stage; hbm_frac: once
         fb64, _ = T.fmm_tucker_storage_bytes(h2, T.FMM_C128)
         rep = {"gamma": gamma, "compress_s": round(t_c, 2), "pass_ms": round(ms, 4), "GBps": round(gbs, 1),
-               "hbm_frac": round(gbs / HBM_PEAK_GBS, 4), "factors_MB_f32": round(fb / 2 ** 20, 1),
+               "hbm_frac": round((2 * b_stage - fac) / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4), "factors_MB_f32": round(fb / 2 ** 20, 1),
                "factors_MB_f64": round(fb64 / 2 ** 20, 1),
                "ranks_mean": [round(float(v), 2) for v in ranks.reshape(-1, 3).mean(0)]}
         if dense_ms:
@@ -599,10 +603,10 @@ def grid_pass(args, T, torch, synth, wg, verts, tris, sample):
         ddis = time_ms(torch, lambda: T.fmm_dense_disaggregate(dplan, T.FMM_C128, dense, 1, g64, V64), reps=5)
         b_stage, fac = tucker_stage_bytes(ranks, lay.offsets, wg.n_theta, wg.n_phi, 8)
         b_d64 = dense_stage_bytes(lay.offsets, wg.n_theta, wg.n_phi, 16)
-        gbs = 2 * b_stage / (ms * 1e-3) / 1e9
+        gbs = 2 * b_stage / (ms * 1e-3) / 1e9  # factors once per stage; hbm_frac: once
         rep = {"workload": wg.name, "grid": [wg.n_theta, wg.n_phi], "compress_s": round(t_c, 2),
                "tucker_pass_ms": round(ms, 4), "tucker_pass_GBps": round(gbs, 1),
-               "hbm_frac": round(gbs / HBM_PEAK_GBS, 4),
+               "hbm_frac": round((2 * b_stage - fac) / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                "dense_pass_ms": round(dagg + ddis, 4),
                "dense_pass_GBps": round(2 * b_d64 / ((dagg + ddis) * 1e-3) / 1e9, 1),
                "speedup_vs_dense_pass": round((dagg + ddis) / ms, 2),
@@ -804,7 +808,7 @@ def svd_comparison(args, T, torch, lay, dense, w, x32, g32, tucker_ms, tucker_fa
         ms = float(np.mean([a.elapsed_time(b) for a, b in evs]))
         b_stage, fac = svd_stage_bytes(rs, lay.offsets, w.n_theta, w.n_phi, 8)
         assert fac == fbytes, (fac, fbytes)
-        gbs = 2 * b_stage / (ms * 1e-3) / 1e9
+        gbs = 2 * b_stage / (ms * 1e-3) / 1e9  # factors once per stage; hbm_frac: once
         rep = {"compress_s": round(t_c, 2), "r_beta_mean": round(float(rs[..., 2].mean()), 2),
                "factors_MB_f32": round(fbytes / 2 ** 20, 1),
                "tucker_factors_MB_f32": round(tucker_fac_bytes / 2 ** 20, 1),

@@ -312,10 +312,10 @@ fmm_status fmm_tucker_disaggregate(fmm_tucker_t h, fmm_prec prec, int32_t nrhs, 
 
 /* One aggregation + disaggregation pass: F = aggregation of x and V = disaggregation
  * of G exactly as fmm_tucker_aggregate and fmm_tucker_disaggregate compute them (same
- * arithmetic, bitwise equal results), with the work of both stages interleaved in
- * longest-first work lists (streaming kernels: one persistent launch that takes the
- * list's entries from a work counter; matrix-core path: four grouped launches per chunk
- * of right-hand sides).  F must not alias G, x or V.  Passes of one handle and
+ * arithmetic, bitwise equal results), with the work of both stages in longest-first work
+ * lists (streaming kernels: one persistent launch that takes the list's entries from a
+ * work counter and reads an item's factors once for both stages; matrix-core path: four
+ * grouped launches per chunk of right-hand sides).  F must not alias G, x or V.  Passes of one handle and
  * precision must not overlap in time (on different streams): they share the work
  * counter, the partial sums and the multi-RHS scratch. */
 fmm_status fmm_tucker_pass(fmm_tucker_t h, fmm_prec prec, int32_t nrhs, const void* x, void* F, const void* G,

@@ -1118,16 +1118,15 @@ __device__ __forceinline__ TuckWork const_load(const TuckWork* p) {
   return __builtin_bit_cast(TuckWork, v);
 }
 
-// One work entry: a unit and a block of at most RB right-hand sides.  The entries of a
+// One work entry: unit iu and block blk of at most RB right-hand sides.  The entries of a
 // unit follow each other, so that the second and later blocks find the factors in the
 // memory-side cache.
 template <typename T, int NT, int JMAX, int RB>
 __device__ __forceinline__ void stream_entry(const StreamArgs<T>& a, const StreamLds<T>& L, unsigned char* smem,
-                                             int entry, int32_t& next_entry) {
+                                             int iu, int blk, int32_t& next_entry) {
   using C = typename Tr<T>::c;
   constexpr int E = Tr<T>::E, NW = NT / 64;
   const int tid = threadIdx.x;
-  const int iu = entry / a.n_rblk, blk = entry - iu * a.n_rblk;
   // (the list is constant while kernels run: scalar loads)
   const TuckWork work = const_load(a.work + iu);
   const TuckUnit& u = work.u;
@@ -1219,7 +1218,7 @@ void tucker_pass_kernel(StreamArgs<T> a) {
   const int total = a.n_units * a.n_rblk;
   if (a.next == nullptr) {
     int32_t none;
-    stream_entry<T, NT, JMAX, RB>(a, L, smem, blockIdx.x, none);
+    stream_entry<T, NT, JMAX, RB>(a, L, smem, blockIdx.x, blockIdx.y, none);
     return;
   }
   int32_t mine = 0;  // (first thread) the next entry, taken when the current one's sweep is done
@@ -1229,7 +1228,8 @@ void tucker_pass_kernel(StreamArgs<T> a) {
     __syncthreads();
     const int i = __builtin_amdgcn_readfirstlane(take);
     if (i >= total) break;  // uniform: every wavefront leaves
-    stream_entry<T, NT, JMAX, RB>(a, L, smem, i, mine);
+    const int iu = i / a.n_rblk;
+    stream_entry<T, NT, JMAX, RB>(a, L, smem, iu, i - iu * a.n_rblk, mine);
     __syncthreads();  // the entry's last LDS reads and `take` are done before the next one
   }
 }
@@ -1400,19 +1400,21 @@ bool stream_fits(const TuckMax& mx, int threads, int nrhs, bool dis, StreamFit* 
 
 template <typename T, int NT, int JMAX, int RB>
 hipError_t launch_stream_kernel(const StreamArgs<T>& a, const StreamFit& f, int64_t entries, hipStream_t s) {
-  unsigned blocks = (unsigned)entries;
+  dim3 grid((unsigned)a.n_units, (unsigned)a.n_rblk);
   if (a.next) {
-    const hipError_t e = persistent_grid(&tucker_pass_kernel<T, NT, JMAX, RB>, NT, f.lds, entries, &blocks);
+    const hipError_t e = persistent_grid(&tucker_pass_kernel<T, NT, JMAX, RB>, NT, f.lds, entries, &grid.x);
     if (e != hipSuccess) return e;
+    grid.y = 1;
   }
-  hipLaunchKernelGGL((tucker_pass_kernel<T, NT, JMAX, RB>), dim3(blocks), dim3(NT), f.lds, s, a);
+  hipLaunchKernelGGL((tucker_pass_kernel<T, NT, JMAX, RB>), grid, dim3(NT), f.lds, s, a);
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_stream(const StreamArgs<T>& a, const StreamFit& f, hipStream_t s) {
+hipError_t launch_stream(StreamArgs<T> a, const StreamFit& f, hipStream_t s) {
   const int64_t entries = (int64_t)a.n_units * a.n_rblk;
-  if (entries > INT32_MAX) return hipErrorInvalidValue;
+  // the counter runs past the entries by one per workgroup
+  if (entries > INT32_MAX / 2) a.next = nullptr;
   TFMM_STREAM_CASE(64, 4, 1)
   TFMM_STREAM_CASE(64, 4, 2)
   TFMM_STREAM_CASE(64, 4, 4)
