@@ -655,8 +655,8 @@ extern "C" fmm_status fmm_tucker_upload(fmm_tucker_t h, fmm_prec prec, void* are
     double c = 0.0;
     for (const TuckUnit& u : P.units) c += item_cost(P.items[u.item]) * (u.b1 - u.b0) / P.items[u.item].rb;
     c /= std::max<size_t>(1, P.units.size());
-    // (measured on MI355X, 1 right-hand side, complex64 pass: mean 15k elements takes 133 us
-    // with 256 threads, 149 with 128 and 204 with 512; 140k takes 118 with 512 and 125 with
+    // (measured on MI355X, 1 right-hand side, complex64 pass: mean 15k elements takes 126 us
+    // with 256 threads, 147 with 128 and 204 with 512; 140k takes 118 with 512 and 125 with
     // 256; 259k 229 with 512 and 321 with 256.  Where the angular operands don't fit LDS, the
     // old line stands.)
     const int t_plain = c >= 1e5 ? 512 : (c >= 3e4 ? 256 : 128);

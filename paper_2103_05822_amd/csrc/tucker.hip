@@ -20,7 +20,7 @@
 //
 // One-right-hand-side pass on an MI355X, before (one read of the factors per stage, angular
 // products on the vector units) and now: 4000 items of mean 15k elements, complex64, 231 and
-// 135 us (510 MB: 3.8 TB/s); 512 items of mean 259k 398 and 230 us (1.2 GB: 5.2 TB/s); both
+// 126 us (510 MB: 4.0 TB/s); 512 items of mean 259k 398 and 230 us (1.2 GB: 5.2 TB/s); both
 // stages alone, complex128, 800 items of mean 58k 472 and 310 us (1.6 GB: 5.2 TB/s).
 #include <hip/hip_runtime.h>
 
@@ -860,10 +860,14 @@ struct StreamLds {
 };
 
 // Rows per step, and steps whose rows are held (one in work, the others being loaded), for
-// J slices per wavefront: 48 to 64 registers of row data a lane, so that a workgroup keeps
-// at least 24 KB of loads in flight.
+// J slices per wavefront: 32 to 64 registers of row data a lane.  One right-hand side's short
+// rows hold 2 steps, for the registers that a fifth wavefront needs; several right-hand sides
+// run at 2 wavefronts a SIMD anyway and hold 3 (5 right-hand sides: 350 us, 352 with 2).
 constexpr int rows_per_step(int J) { return J == 1 ? 4 : (J == 2 ? 2 : 1); }
-constexpr int steps_held(int J, int RB, bool f64) { return J > 4 ? 2 : (J == 4 ? (f64 ? 2 : 3) : 3); }
+constexpr int steps_held(int J, int RB, bool f64) {
+  if (J > 4 || (J == 4 && f64)) return 2;
+  return J <= 2 && RB == 1 ? 2 : 3;
+}
 
 __device__ __forceinline__ float4 pkeep(float4 v, bool k) {
   return make_float4(k ? v.x : 0.f, k ? v.y : 0.f, k ? v.z : 0.f, k ? v.w : 0.f);
@@ -1171,7 +1175,12 @@ __device__ __forceinline__ void stream_entry(const StreamArgs<T>& a, const Strea
   }
   const int ns = ((it.ld_ub / E + 63) >> 6) + ((it.ld_c / E + 63) >> 6);
   const int j = (ns + NW - 1) / NW;
-  if constexpr (JMAX == 4) {
+  if constexpr (JMAX == 2) {
+    if (j <= 1)
+      sweep_unit<T, NT, 1, RB>(a, it, u, r0, nr, vec, L.row, red);
+    else
+      sweep_unit<T, NT, 2, RB>(a, it, u, r0, nr, vec, L.row, red);
+  } else if constexpr (JMAX == 4) {
     if (j <= 1)
       sweep_unit<T, NT, 1, RB>(a, it, u, r0, nr, vec, L.row, red);
     else if (j == 2)
@@ -1210,7 +1219,8 @@ __device__ __forceinline__ void stream_entry(const StreamArgs<T>& a, const Strea
 // slot only tens of microseconds after a unit of a small-box layout ended).  A stage
 // alone runs one workgroup per entry.
 template <typename T, int NT, int JMAX, int RB>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(JMAX == 4 && RB == 1 ? 4 : 2)))
+__global__ __launch_bounds__(NT)
+__attribute__((amdgpu_waves_per_eu(RB > 1 || JMAX > 4 ? 2 : (JMAX == 2 ? 5 : 4))))
 void tucker_pass_kernel(StreamArgs<T> a) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int32_t take;
@@ -1377,11 +1387,17 @@ size_t tucker_lds_bytes(const TuckMax& mx) {
 // threads, 16.  2 or 4 right-hand sides share a read of the factors where the row allows
 // 4 slices.  The angular operands are staged in LDS while a CU still holds
 // kStageMinWaves wavefronts.
+//
+// Small complex64 items are bound by the latency of each unit's phases, which more workgroups
+// on a CU hide.  With at most 2 slices the kernel fits 96 registers, so 5 wavefronts a SIMD
+// (4000 items of mean 15k: 135 us with 4, 126 with 5; 6 spill, 134).  With 512
+// threads 5 a SIMD hold no more workgroups than 4; in complex128 it was not tried.
 template <typename T>
 bool stream_fits(const TuckMax& mx, int threads, int nrhs, bool dis, StreamFit* out) {
   for (; threads <= 512; threads *= 2) {
     const int nw = threads / 64, j = (mx.slices + nw - 1) / nw;
-    const int jmax = j <= 4 ? 4 : (j <= 8 ? 8 : (j <= 16 && threads == 512 ? 16 : 0));
+    const bool small = j <= 2 && nrhs == 1 && threads <= 256 && sizeof(T) == 4;
+    const int jmax = small ? 2 : (j <= 4 ? 4 : (j <= 8 ? 8 : (j <= 16 && threads == 512 ? 16 : 0)));
     if (!jmax) continue;
     for (int rb = jmax == 4 && nrhs > 1 ? (nrhs == 2 ? 2 : 4) : 1; rb >= 1; rb /= 2) {
       const size_t staged = StreamLds<T>(mx, nw, rb, true, dis).bytes();
@@ -1415,6 +1431,11 @@ hipError_t launch_stream(StreamArgs<T> a, const StreamFit& f, hipStream_t s) {
   const int64_t entries = (int64_t)a.n_units * a.n_rblk;
   // the counter runs past the entries by one per workgroup
   if (entries > INT32_MAX / 2) a.next = nullptr;
+  if constexpr (sizeof(T) == 4) {
+    TFMM_STREAM_CASE(64, 2, 1)
+    TFMM_STREAM_CASE(128, 2, 1)
+    TFMM_STREAM_CASE(256, 2, 1)
+  }
   TFMM_STREAM_CASE(64, 4, 1)
   TFMM_STREAM_CASE(64, 4, 2)
   TFMM_STREAM_CASE(64, 4, 4)
