@@ -9,6 +9,9 @@
 // imaginary parts of 8 right-hand sides), which leaves the vector registers to loads in
 // flight.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
+
 #include "cplx.hpp"
 #include "kernels.hpp"
 
@@ -93,7 +96,7 @@ __global__ __launch_bounds__(kThreads) void dense_agg_kernel(const typename Tr<T
 //   disaggregation Re A [Re G, Im G]  +  Im A [ Im G, -Re G]   (conj A)
 // whose second operand is the neighbouring lane's value, negated in one parity.  Columns
 // past the last right-hand side read a clamped one and are not stored.  200 groups of 232
-// rows and 2450 columns, complex128, 8 right-hand sides, both stages: 769 us (4.9 TB/s);
+// rows and 2450 columns, complex128, 8 right-hand sides, both stages: 745 us (5.0 TB/s);
 // 940 us with the products on the vector units, whose 64 sums a thread left two wavefronts
 // a SIMD to hide the loads.
 template <typename T>
@@ -198,49 +201,99 @@ __global__ __launch_bounds__(kThreads) void dense_agg_mfma_kernel(const typename
     }
 }
 
-// Disaggregation: a wavefront takes a block of up to 16 rows of one group for up to 8
-// right-hand sides and walks the columns in steps of 4.  The plan orders the blocks so that
-// each XCD works on a few groups at a time, whose G then stays in its L2 (it is read once
-// per block, half the bytes of A's).
+// A 16-byte pack of a row of A or an element of it, read at the element's alignment.
 template <typename T>
-__global__ __launch_bounds__(64) void dense_disagg_mfma_kernel(const typename Tr<T>::c* __restrict__ A,
-                                                               const DenseBlock* __restrict__ blocks, int ncols,
-                                                               int nrhs, const typename Tr<T>::c* __restrict__ Gin,
-                                                               typename Tr<T>::c* __restrict__ V) {
+struct RowPack;
+template <>
+struct RowPack<float> {
+  typedef float v __attribute__((ext_vector_type(4), aligned(8)));
+};
+template <>
+struct RowPack<double> {
+  typedef double v __attribute__((ext_vector_type(2), aligned(16)));
+};
+
+// Disaggregation: a workgroup takes a block of up to 16 rows of one group for up to 8
+// right-hand sides; its eight wavefronts take chunks of columns in turn and meet in LDS.  The
+// plan orders the blocks so that each XCD works on a few groups at a time, whose G then stays
+// in its L2 (it is read once per block, half the bytes of A's).
+//
+// Lane (li, kg) reads kPacks packs of 16 bytes of row li a chunk, neighbouring kg's adjacent:
+// 64 bytes of a row an instruction.  Both A and B take the packs' columns as the K index, so
+// their order is free.  Each pack, wavefront and part of A has its own accumulators, 64 in
+// all, that meet in a tree: a chain is as long as that of 64 lanes which share a row, and so
+// is its rounding error.  8 right-hand sides, complex64 / complex128: 24 groups of mean 909
+// rows and 5700 columns take 228 / 391 us (4.4 / 5.1 TB/s), two such groups 27 / 44 us; with
+// one wavefront a block, reads of one element and one accumulator a part they took 762 / 400
+// and 473 / 211 us, and the error was five to ten times as large.
+constexpr int kDisThreads = 512;
+constexpr int kDisWaves = kDisThreads / 64;
+template <typename T>
+__global__ __launch_bounds__(kDisThreads) void dense_disagg_mfma_kernel(const typename Tr<T>::c* __restrict__ A,
+                                                                        const DenseBlock* __restrict__ blocks,
+                                                                        int ncols, int nrhs,
+                                                                        const typename Tr<T>::c* __restrict__ Gin,
+                                                                        typename Tr<T>::c* __restrict__ V) {
   using C = typename Tr<T>::c;
   using Acc = typename DenseMfma<T>::acc;
-  constexpr int U = 8;  // steps in flight
-  const int lane = threadIdx.x, li = lane & 15, kg = lane >> 4;
+  using Pack = typename RowPack<T>::v;
+  constexpr int E = Tr<T>::E;
+  constexpr int kPacks = 4;
+  constexpr int kChunk = 4 * E * kPacks;  // columns of a wavefront's step
+  __shared__ T sum[kDisWaves - 1][4][64];
+  const int lane = threadIdx.x & 63, li = lane & 15, kg = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const DenseBlock b = blocks[blockIdx.x];
   const int r0 = blockIdx.y * 8, nr = min(8, nrhs - r0);
   const C* row = A + (b.row0 + min(li, b.rows - 1)) * ncols;
   const T* gv = reinterpret_cast<const T*>(Gin + (int64_t)b.group * ncols * nrhs + r0) + min(li, 2 * nr - 1);
-  Acc acc[2] = {Acc{0, 0, 0, 0}, Acc{0, 0, 0, 0}};
-  for (int c0 = 0; c0 < ncols; c0 += 4 * U) {
-    C a[U];
-    T gt[U];
+  Acc acc[kPacks][2];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int c = c0 + 4 * u + kg, cc = min(c, ncols - 1);
-      a[u] = row[cc];
-      gt[u] = gv[(int64_t)cc * 2 * nrhs];
-      if (c >= ncols) {
-        a[u] = czero<C>();
-        gt[u] = T(0);
+  for (int q = 0; q < kPacks; ++q) acc[q][0] = acc[q][1] = Acc{0, 0, 0, 0};
+  // (ncols counts both polarisations, so it is even and a complex64 pack is whole or absent)
+  auto chunk = [&](int c0, auto tail) {
+    Pack a[kPacks];
+    T g[kPacks][E];
+#pragma unroll
+    for (int q = 0; q < kPacks; ++q) {
+      const int c = c0 + (4 * q + kg) * E, cc = tail ? min(c, ncols - E) : c;
+      a[q] = *reinterpret_cast<const Pack*>(row + cc);
+#pragma unroll
+      for (int e = 0; e < E; ++e) g[q][e] = gv[(int64_t)(cc + e) * 2 * nrhs];
+      if (tail && c >= ncols) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) a[q][2 * e] = a[q][2 * e + 1] = g[q][e] = T(0);
       }
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const T o = other_part(gt[u]), g2 = li & 1 ? -o : o;
-      acc[0] = DenseMfma<T>::mul(a[u].x, gt[u], acc[0]);
-      acc[1] = DenseMfma<T>::mul(a[u].y, g2, acc[1]);
-    }
+    for (int e = 0; e < E; ++e)
+#pragma unroll
+      for (int q = 0; q < kPacks; ++q) {
+        const T o = other_part(g[q][e]), g2 = li & 1 ? -o : o;
+        acc[q][0] = DenseMfma<T>::mul(a[q][2 * e], g[q][e], acc[q][0]);
+        acc[q][1] = DenseMfma<T>::mul(a[q][2 * e + 1], g2, acc[q][1]);
+      }
+  };
+  int c0 = kChunk * w;
+  for (; c0 + kChunk <= ncols; c0 += kChunk * kDisWaves) chunk(c0, std::false_type{});
+  if (c0 < ncols) chunk(c0, std::true_type{});
+  T v[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    v[i] = ((acc[0][0][i] + acc[0][1][i]) + (acc[1][0][i] + acc[1][1][i])) +
+           ((acc[2][0][i] + acc[2][1][i]) + (acc[3][0][i] + acc[3][1][i]));
+  if (w > 0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sum[w - 1][i][lane] = v[i];
   }
-  if (li >= 2 * nr) return;
+  __syncthreads();
+  if (w > 0 || li >= 2 * nr) return;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int m = DenseMfma<T>::row(i, kg);
-    if (m < b.rows) reinterpret_cast<T*>(V + (b.row0 + m) * nrhs + r0)[li] = acc[0][i] + acc[1][i];
+    const T s = ((v[i] + sum[0][i][lane]) + (sum[1][i][lane] + sum[2][i][lane])) +
+                ((sum[3][i][lane] + sum[4][i][lane]) + (sum[5][i][lane] + sum[6][i][lane]));
+    if (m < b.rows) reinterpret_cast<T*>(V + (b.row0 + m) * nrhs + r0)[li] = s;
   }
 }
 
@@ -322,7 +375,7 @@ hipError_t launch_dense_disagg(const void* A, const int64_t* offsets, int n_grou
     return hipGetLastError();
   }
   if (n_blocks <= 0 || row_blocks == nullptr) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((dense_disagg_mfma_kernel<T>), dim3((unsigned)n_blocks, (nrhs + 7) / 8), dim3(64), 0, s,
+  hipLaunchKernelGGL((dense_disagg_mfma_kernel<T>), dim3((unsigned)n_blocks, (nrhs + 7) / 8), dim3(kDisThreads), 0, s,
                      static_cast<const C*>(A), row_blocks, ncols, nrhs, static_cast<const C*>(G), static_cast<C*>(V));
   return hipGetLastError();
 }
