@@ -1152,9 +1152,11 @@ extern "C" fmm_status fmm_dense_aggregate(fmm_dense_t d, fmm_prec prec, const vo
   const int ncols = 2 * d->layout.ndir();
   hipStream_t hs = static_cast<hipStream_t>(stream);
   if (prec == FMM_C128)
-    TFMM_HIP(launch_dense_agg<double>(farfield, d->d_groups, d->layout.n_groups, ncols, nrhs, x, F, hs));
+    TFMM_HIP(launch_dense_agg<double>(farfield, d->d_groups, d->layout.n_groups, d->layout.n_basis(), ncols, nrhs,
+                                      x, F, hs));
   else
-    TFMM_HIP(launch_dense_agg<float>(farfield, d->d_groups, d->layout.n_groups, ncols, nrhs, x, F, hs));
+    TFMM_HIP(launch_dense_agg<float>(farfield, d->d_groups, d->layout.n_groups, d->layout.n_basis(), ncols, nrhs, x,
+                                     F, hs));
   return FMM_OK;
 }
 

@@ -7,7 +7,7 @@
 // lane, the disaggregation a row per wavefront.  With more, up to 8 right-hand sides share
 // a read of A and the products run on the matrix cores (16 real columns hold the real and
 // imaginary parts of 8 right-hand sides), which leaves the vector registers to loads in
-// flight.
+// flight; the aggregation of groups of few rows stays on the vector units for up to 4.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -86,6 +86,69 @@ __global__ __launch_bounds__(kThreads) void dense_agg_kernel(const typename Tr<T
 
 // ---------------------------------------------------- several right-hand sides
 //
+// Aggregation of groups of few rows for 2 to 4 right-hand sides (RB columns held, nr of them
+// valid): a thread walks all rows of two columns.  Such a group's output is as long as its
+// input, and the matrix cores' tiles store a quarter of a line at a time: 200 groups of 8 rows
+// and 5700 columns, 2 and 4 right-hand sides, complex128 30 and 42 us, 59 with those tiles;
+// complex64 17 and 25 us, 33.  32 rows: complex128 124 and 138 us, 112 and 120 with the tiles;
+// complex64 51 and 66, 53 and 56 (3000 groups of 40 rows and 196 columns, 2 right-hand sides:
+// 40, 47; of 20 rows, complex128, 3: 41, 53).  Rows of few columns leave most of its threads
+// idle (20000 groups of 9 rows and 30 columns, complex64, 3 right-hand sides: 64, 36).
+template <typename T>
+bool few_rows(int64_t n_rows, int n_groups, int ncols, int nrhs) {
+  const int rows = sizeof(T) == 8 ? 24 : (nrhs == 2 ? 40 : 20);
+  return nrhs <= 4 && ncols > 128 && n_rows <= (int64_t)rows * n_groups;
+}
+constexpr int kFewCols = 2;  // columns per thread
+template <typename T, int RB>
+__global__ __launch_bounds__(kThreads) void dense_agg_few_kernel(const typename Tr<T>::c* __restrict__ A,
+                                                                 const DenseGroup* __restrict__ groups, int n_chunks,
+                                                                 int ncols, int nrhs,
+                                                                 const typename Tr<T>::c* __restrict__ x,
+                                                                 typename Tr<T>::c* __restrict__ F) {
+  using C = typename Tr<T>::c;
+  constexpr int U = RB == 4 ? 2 : 4;  // rows in flight
+  const int g = blockIdx.x / n_chunks;
+  const int c0 = (blockIdx.x - g * n_chunks) * kThreads * kFewCols + threadIdx.x;
+  const DenseGroup grp = groups[g];
+  C acc[kFewCols][RB];
+  int off[kFewCols];
+#pragma unroll
+  for (int j = 0; j < kFewCols; ++j) {
+    off[j] = min(c0 + kThreads * j, ncols - 1);  // (columns past the end are not stored)
+#pragma unroll
+    for (int r = 0; r < RB; ++r) acc[j][r] = czero<C>();
+  }
+  const C* base = A + grp.row0 * ncols;
+  const C* xb = x + grp.row0 * nrhs;
+  auto rows = [&](int n, auto count) {
+    C a[count][kFewCols];
+#pragma unroll
+    for (int u = 0; u < count; ++u)
+#pragma unroll
+      for (int j = 0; j < kFewCols; ++j) a[u][j] = base[(int64_t)(n + u) * ncols + off[j]];
+#pragma unroll
+    for (int u = 0; u < count; ++u)
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        const C xn = r < nrhs ? xb[(int64_t)(n + u) * nrhs + r] : czero<C>();
+#pragma unroll
+        for (int j = 0; j < kFewCols; ++j) cfma(acc[j][r], a[u][j], xn);
+      }
+  };
+  int n = 0;
+  for (; n + U <= grp.nb; n += U) rows(n, std::integral_constant<int, U>{});
+  for (; n < grp.nb; ++n) rows(n, std::integral_constant<int, 1>{});
+#pragma unroll
+  for (int j = 0; j < kFewCols; ++j) {
+    if (c0 + kThreads * j >= ncols) continue;
+    C* out = F + ((int64_t)g * ncols + c0 + kThreads * j) * nrhs;
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+      if (r < nrhs) out[r] = acc[j][r];
+  }
+}
+
 // FP32 and FP64 matrix instructions of 16 x 16 x 4: lane l feeds row (column) l % 16 and
 // k = l / 16 of A (B); register i of lane l holds column l % 16 of row 4 (l / 16) + i
 // (FP32) or 4 i + l / 16 (FP64).  Column 2 r + q of B is part q (real, imaginary) of
@@ -343,7 +406,7 @@ __global__ __launch_bounds__(kThreads) void dense_disagg_kernel(const typename T
 }  // namespace
 
 template <typename T>
-hipError_t launch_dense_agg(const void* A, const DenseGroup* groups, int n_groups, int ncols, int nrhs,
+hipError_t launch_dense_agg(const void* A, const DenseGroup* groups, int n_groups, int64_t n_rows, int ncols, int nrhs,
                             const void* x, void* F, hipStream_t s) {
   using C = typename Tr<T>::c;
   if (n_groups == 0) return hipSuccess;
@@ -352,6 +415,11 @@ hipError_t launch_dense_agg(const void* A, const DenseGroup* groups, int n_group
     hipLaunchKernelGGL(dense_agg_kernel<T>, dim3((unsigned)n_groups * n_chunks), dim3(kThreads), 0, s,
                        static_cast<const C*>(A), groups, n_chunks, ncols, static_cast<const C*>(x),
                        static_cast<C*>(F));
+  } else if (few_rows<T>(n_rows, n_groups, ncols, nrhs)) {
+    const int n_chunks = (ncols + kThreads * kFewCols - 1) / (kThreads * kFewCols);
+    hipLaunchKernelGGL((nrhs == 2 ? dense_agg_few_kernel<T, 2> : dense_agg_few_kernel<T, 4>),
+                       dim3((unsigned)n_groups * n_chunks), dim3(kThreads), 0, s, static_cast<const C*>(A), groups,
+                       n_chunks, ncols, nrhs, static_cast<const C*>(x), static_cast<C*>(F));
   } else {
     const int n_chunks = (ncols + 63) / 64;
     hipLaunchKernelGGL(dense_agg_mfma_kernel<T>, dim3((unsigned)n_groups * n_chunks, (nrhs + 7) / 8), dim3(kThreads),
@@ -380,10 +448,10 @@ hipError_t launch_dense_disagg(const void* A, const int64_t* offsets, int n_grou
   return hipGetLastError();
 }
 
-template hipError_t launch_dense_agg<float>(const void*, const DenseGroup*, int, int, int, const void*, void*,
-                                            hipStream_t);
-template hipError_t launch_dense_agg<double>(const void*, const DenseGroup*, int, int, int, const void*, void*,
-                                             hipStream_t);
+template hipError_t launch_dense_agg<float>(const void*, const DenseGroup*, int, int64_t, int, int, const void*,
+                                            void*, hipStream_t);
+template hipError_t launch_dense_agg<double>(const void*, const DenseGroup*, int, int64_t, int, int, const void*,
+                                             void*, hipStream_t);
 template hipError_t launch_dense_disagg<float>(const void*, const int64_t*, int, int64_t, const DenseBlock*, int,
                                                int, int, const void*, void*, hipStream_t);
 template hipError_t launch_dense_disagg<double>(const void*, const int64_t*, int, int64_t, const DenseBlock*, int,

@@ -50,7 +50,7 @@ hipError_t launch_zero_rows(size_t elem_bytes, void* base, const int32_t* rows, 
 
 // Dense (plain) aggregation / disaggregation.
 template <typename T>
-hipError_t launch_dense_agg(const void* A, const DenseGroup* groups, int n_groups, int ncols, int nrhs,
+hipError_t launch_dense_agg(const void* A, const DenseGroup* groups, int n_groups, int64_t n_rows, int ncols, int nrhs,
                             const void* x, void* F, hipStream_t s);
 template <typename T>
 hipError_t launch_dense_disagg(const void* A, const int64_t* offsets, int n_groups, int64_t n_rows,
