@@ -10,6 +10,7 @@
 // flight; the aggregation of groups of few rows stays on the vector units for up to 4.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "cplx.hpp"
@@ -405,28 +406,34 @@ __global__ __launch_bounds__(kThreads) void dense_disagg_kernel(const typename T
 
 }  // namespace
 
+// Workgroups of one launch along x (a grid holds fewer than 2^32 threads); layouts of more run
+// as several launches.
+constexpr int kMaxGrid = 1 << 22;
+
 template <typename T>
 hipError_t launch_dense_agg(const void* A, const DenseGroup* groups, int n_groups, int64_t n_rows, int ncols, int nrhs,
                             const void* x, void* F, hipStream_t s) {
   using C = typename Tr<T>::c;
-  if (n_groups == 0) return hipSuccess;
-  if (nrhs == 1) {
-    const int n_chunks = (ncols + 128 * Tr<T>::E - 1) / (128 * Tr<T>::E);
-    hipLaunchKernelGGL(dense_agg_kernel<T>, dim3((unsigned)n_groups * n_chunks), dim3(kThreads), 0, s,
-                       static_cast<const C*>(A), groups, n_chunks, ncols, static_cast<const C*>(x),
-                       static_cast<C*>(F));
-  } else if (few_rows<T>(n_rows, n_groups, ncols, nrhs)) {
-    const int n_chunks = (ncols + kThreads * kFewCols - 1) / (kThreads * kFewCols);
-    hipLaunchKernelGGL((nrhs == 2 ? dense_agg_few_kernel<T, 2> : dense_agg_few_kernel<T, 4>),
-                       dim3((unsigned)n_groups * n_chunks), dim3(kThreads), 0, s, static_cast<const C*>(A), groups,
-                       n_chunks, ncols, nrhs, static_cast<const C*>(x), static_cast<C*>(F));
-  } else {
-    const int n_chunks = (ncols + 63) / 64;
-    hipLaunchKernelGGL(dense_agg_mfma_kernel<T>, dim3((unsigned)n_groups * n_chunks, (nrhs + 7) / 8), dim3(kThreads),
-                       0, s, static_cast<const C*>(A), groups, n_chunks, ncols, nrhs, static_cast<const C*>(x),
-                       static_cast<C*>(F));
+  const bool few = few_rows<T>(n_rows, n_groups, ncols, nrhs);
+  const int cols = nrhs == 1 ? 128 * Tr<T>::E : (few ? kThreads * kFewCols : 64);  // of a workgroup
+  const int n_chunks = (ncols + cols - 1) / cols, step = std::max(1, kMaxGrid / n_chunks);
+  const C* a = static_cast<const C*>(A);
+  const C* xv = static_cast<const C*>(x);
+  hipError_t e = hipSuccess;
+  for (int64_t g0 = 0; g0 < n_groups && e == hipSuccess; g0 += step) {
+    const unsigned blocks = (unsigned)std::min<int64_t>(step, n_groups - g0) * n_chunks;
+    C* f = static_cast<C*>(F) + g0 * ncols * nrhs;
+    if (nrhs == 1)
+      hipLaunchKernelGGL(dense_agg_kernel<T>, dim3(blocks), dim3(kThreads), 0, s, a, groups + g0, n_chunks, ncols, xv, f);
+    else if (few)
+      hipLaunchKernelGGL((nrhs == 2 ? dense_agg_few_kernel<T, 2> : dense_agg_few_kernel<T, 4>), dim3(blocks),
+                         dim3(kThreads), 0, s, a, groups + g0, n_chunks, ncols, nrhs, xv, f);
+    else
+      hipLaunchKernelGGL(dense_agg_mfma_kernel<T>, dim3(blocks, (nrhs + 7) / 8), dim3(kThreads), 0, s, a, groups + g0,
+                         n_chunks, ncols, nrhs, xv, f);
+    e = hipGetLastError();
   }
-  return hipGetLastError();
+  return e;
 }
 
 template <typename T>
@@ -443,9 +450,15 @@ hipError_t launch_dense_disagg(const void* A, const int64_t* offsets, int n_grou
     return hipGetLastError();
   }
   if (n_blocks <= 0 || row_blocks == nullptr) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((dense_disagg_mfma_kernel<T>), dim3((unsigned)n_blocks, (nrhs + 7) / 8), dim3(kDisThreads), 0, s,
-                     static_cast<const C*>(A), row_blocks, ncols, nrhs, static_cast<const C*>(G), static_cast<C*>(V));
-  return hipGetLastError();
+  hipError_t e = hipSuccess;
+  for (int64_t b0 = 0; b0 < n_blocks && e == hipSuccess; b0 += kMaxGrid) {
+    const unsigned blocks = (unsigned)std::min<int64_t>(kMaxGrid, n_blocks - b0);
+    hipLaunchKernelGGL((dense_disagg_mfma_kernel<T>), dim3(blocks, (nrhs + 7) / 8), dim3(kDisThreads), 0, s,
+                       static_cast<const C*>(A), row_blocks + b0, ncols, nrhs, static_cast<const C*>(G),
+                       static_cast<C*>(V));
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 template hipError_t launch_dense_agg<float>(const void*, const DenseGroup*, int, int64_t, int, int, const void*,
