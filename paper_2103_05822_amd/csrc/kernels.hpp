@@ -26,6 +26,8 @@ size_t tucker_lds_bytes(const TuckMax& mx);
 // kernels stage the angular operands in LDS.
 constexpr size_t kCuLds = 160 * 1024;
 constexpr int kStageMinWaves = 8;
+// LDS that the row-streaming kernel takes besides its dynamic block (its work counter's copy).
+constexpr size_t kPassStaticLds = 16;
 // The row-streaming kernel that a layout takes: workgroup size, slices per wavefront,
 // right-hand sides per read of the factors, staging, LDS bytes.  `dis`: with the
 // disaggregation.

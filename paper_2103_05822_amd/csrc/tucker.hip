@@ -1223,7 +1223,7 @@ __global__ __launch_bounds__(NT)
 __attribute__((amdgpu_waves_per_eu(RB > 1 || JMAX > 4 ? 2 : (JMAX == 2 ? 5 : 4))))
 void tucker_pass_kernel(StreamArgs<T> a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int32_t take;
+  __shared__ int32_t take;  // (kPassStaticLds)
   const StreamLds<T> L(a.mx, NT / 64, RB, a.staged, a.G != nullptr);
   const int total = a.n_units * a.n_rblk;
   if (a.next == nullptr) {
@@ -1402,11 +1402,12 @@ bool stream_fits(const TuckMax& mx, int threads, int nrhs, bool dis, StreamFit* 
     for (int rb = jmax == 4 && nrhs > 1 ? (nrhs == 2 ? 2 : 4) : 1; rb >= 1; rb /= 2) {
       const size_t staged = StreamLds<T>(mx, nw, rb, true, dis).bytes();
       const size_t plain = StreamLds<T>(mx, nw, rb, false, dis).bytes();
-      if (plain > (size_t)mx.lds) continue;
+      if (plain + kPassStaticLds > (size_t)mx.lds) continue;
       out->threads = threads;
       out->jmax = jmax;
       out->rb = rb;
-      out->staged = mx.stage && staged <= (size_t)mx.lds && (int)(kCuLds / staged) * nw >= kStageMinWaves;
+      out->staged = mx.stage && staged + kPassStaticLds <= (size_t)mx.lds &&
+                    (int)(kCuLds / (staged + kPassStaticLds)) * nw >= kStageMinWaves;
       out->lds = out->staged ? staged : plain;
       return true;
     }

@@ -1,0 +1,57 @@
+"""The rule that picks the row-streaming kernel (host code, no GPU): its LDS counts what the
+kernel declares itself."""
+import ctypes
+
+import pytest
+
+T = pytest.importorskip("paper_2103_05822_amd", reason="libtuckfmm.so not built")
+
+LDS = 160 * 1024
+STATIC = 16   # the pass kernel's own variable, rounded to its alignment
+
+
+class TuckMax(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in
+                ("nb", "rt", "rp", "rb", "q", "t3", "nt", "np", "row", "slices", "lds", "stage")]
+
+
+class StreamFit(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("threads", "jmax", "rb", "staged")] + [("lds", ctypes.c_size_t)]
+
+
+def fits(prec, mx, threads, nrhs, dis=True):
+    name = "_ZN7tuckfmm11stream_fitsI%sEEbRKNS_7TuckMaxEiibPNS_9StreamFitE" % ("d" if prec == "c128" else "f")
+    fn = getattr(ctypes.CDLL(T.binding.LIB_PATH), name)
+    fn.restype = ctypes.c_bool
+    fn.argtypes = [ctypes.POINTER(TuckMax), ctypes.c_int, ctypes.c_int, ctypes.c_bool, ctypes.POINTER(StreamFit)]
+    out = StreamFit()
+    return out if fn(ctypes.byref(mx), threads, nrhs, dis, ctypes.byref(out)) else None
+
+
+def layout(prec, nb, rt, rp, rb, nt, npn, stage=1):
+    """One item's maxima, as the library forms them (phi first: the smaller intermediate)."""
+    E = 1 if prec == "c128" else 2
+    up = lambda v: (v + E - 1) // E * E  # noqa: E731
+    ld_u, ld_c = up(nb), up(rt * rp)
+    theta, phi = nt * rp * (rt + npn), rt * npn * (rp + nt)
+    return TuckMax(nb, rt, rp, rb, rt * rp, nt * rp if theta <= phi else rt * npn, nt, npn, ld_u + ld_c,
+                   -(-(ld_u // E) // 64) - (-(ld_c // E) // 64), LDS, stage)
+
+
+@pytest.mark.parametrize("prec", ["c64", "c128"])
+def test_lds_at_the_limit(prec):
+    # 512 threads, unstaged: row + inter fill the LDS but for the partial sums and `spare` bytes
+    es, real = (8, 4) if prec == "c64" else (16, 8)
+    red = 2 * 8 * 16 * real
+    total = (LDS - red) // es                 # complex values
+    seen = []
+    for spare in (0, 8, 16, 24, 32, 64):
+        mx = layout(prec, 64, 2, 2, 4, 7, 11, stage=0)
+        mx.t3 = 4000
+        mx.row = (total - mx.t3) - spare // es // 2 * 2
+        f = fits(prec, mx, 512, 1)
+        if f is not None:
+            assert f.lds + STATIC <= LDS
+        seen.append(f is not None)
+    assert not seen[0] and seen[-1]
+
