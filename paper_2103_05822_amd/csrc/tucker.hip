@@ -844,6 +844,7 @@ template <typename T>
 struct StreamLds {
   int vecs, row, inter, gs, us, red;
   static constexpr int kRedValues = 16;  // dot products of a step per right-hand side, at most
+  static constexpr int kTooLarge = 1 << 28;
   __host__ __device__ __forceinline__ StreamLds(const TuckMax& mx, int nw, int rb, bool staged, bool dis)
       : vecs(rb),
         row(round_up(mx.row, 2)),
@@ -851,8 +852,10 @@ struct StreamLds {
         gs(staged && dis ? round_up(mx.nt * mx.np, 2) : 0),
         us(staged ? staged_factors(mx) : 0),
         red(nw > 1 ? 2 * nw * kRedValues * rb * (int)sizeof(T) : 0) {}
+  // (a grid of millions of angles times a rank passes an int; a size beyond any LDS stands for it)
   static __host__ __device__ __forceinline__ int staged_factors(const TuckMax& mx) {
-    return round_up(mx.nt * (mx.rt | 1), 2) + round_up(mx.np * (mx.rp | 1), 2);
+    const int64_t n = (((int64_t)mx.nt * (mx.rt | 1) + 1) & ~1ll) + (((int64_t)mx.np * (mx.rp | 1) + 1) & ~1ll);
+    return n < kTooLarge ? (int)n : kTooLarge;
   }
   __host__ __device__ size_t bytes() const {
     return ((size_t)vecs * row + inter + gs + us) * sizeof(typename Tr<T>::c) + red;

@@ -1,5 +1,5 @@
 """The rule that picks the row-streaming kernel (host code, no GPU): its LDS counts what the
-kernel declares itself."""
+kernel declares itself, and sizes beyond an int are not taken for small ones."""
 import ctypes
 
 import pytest
@@ -55,3 +55,11 @@ def test_lds_at_the_limit(prec):
         seen.append(f is not None)
     assert not seen[0] and seen[-1]
 
+
+@pytest.mark.parametrize("prec", ["c64", "c128"])
+@pytest.mark.parametrize("dis", [True, False])
+def test_staging_of_huge_grids(prec, dis):
+    # n_theta r_theta = 2^32 + 1: as a 32-bit product it is 1
+    mx = layout(prec, 1000, 641, 1, 9, 6700417, 1)
+    f = fits(prec, mx, 256, 1, dis)
+    assert f is not None and not f.staged
