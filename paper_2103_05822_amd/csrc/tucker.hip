@@ -863,12 +863,15 @@ struct StreamLds {
 };
 
 // Rows per step, and steps whose rows are held (one in work, the others being loaded), for
-// J slices per wavefront: 32 to 64 registers of row data a lane.  One right-hand side's short
-// rows hold 2 steps, for the registers that a fifth wavefront needs; several right-hand sides
-// run at 2 wavefronts a SIMD anyway and hold 3 (5 right-hand sides: 350 us, 352 with 2).
+// J slices per wavefront: 32 to 120 registers of row data a lane.  One right-hand side's short
+// rows hold 2 steps, for the registers that a fifth wavefront needs.  A row of 5 slices and
+// more keeps one workgroup on a CU, so its own loads must cover their latency: 3 steps, as
+// long as nothing spills (with 2 steps, instances for 8, 10 and 16 slices only and the vector
+// in LDS, one of which spilled, 140 items of mean 1.7M elements, complex64, 2911 us, now 797;
+// and 200 of mean 260k, complex128, 386 us, now 278; one read a stage took 931 and 324 us).
 constexpr int rows_per_step(int J) { return J == 1 ? 4 : (J == 2 ? 2 : 1); }
 constexpr int steps_held(int J, int RB, bool f64) {
-  if (J > 4 || (J == 4 && f64)) return 2;
+  if (J > 10 || (J == 4 && f64)) return 2;
   return J <= 2 && RB == 1 ? 2 : 3;
 }
 
@@ -899,7 +902,7 @@ __device__ __forceinline__ void sweep_rows(const typename Tr<T>::pack* ub, const
   constexpr int NW = NT / 64;
   constexpr int KR = rows_per_step(J), D = steps_held(J, RB, sizeof(T) == 8);
   constexpr int NV = 4 * KR * RB;
-  constexpr bool kVecRegs = RB == 1 && J <= 4;
+  constexpr bool kVecRegs = RB == 1;
   constexpr int kAux = NT >= 256 ? 2 : 0;  // non-temporal
   static_assert(NV <= 64 && NV <= StreamLds<T>::kRedValues * RB, "dot products per step");
   const int nsu = (npu + 63) >> 6, ns = nsu + ((npc + 63) >> 6);
@@ -1193,16 +1196,25 @@ __device__ __forceinline__ void stream_entry(const StreamArgs<T>& a, const Strea
     else
       sweep_unit<T, NT, 4, RB>(a, it, u, r0, nr, vec, L.row, red);
   } else {
+    // (a slice more than the row has is loaded and not used)
     if (j <= 2)
       sweep_unit<T, NT, 2, RB>(a, it, u, r0, nr, vec, L.row, red);
     else if (j <= 4)
       sweep_unit<T, NT, 4, RB>(a, it, u, r0, nr, vec, L.row, red);
-    else if (j <= 6 || JMAX == 8)
-      sweep_unit<T, NT, JMAX == 8 ? 8 : 6, RB>(a, it, u, r0, nr, vec, L.row, red);
+    else if (j == 5)
+      sweep_unit<T, NT, 5, RB>(a, it, u, r0, nr, vec, L.row, red);
+    else if (j == 6)
+      sweep_unit<T, NT, 6, RB>(a, it, u, r0, nr, vec, L.row, red);
+    else if (j == 7)
+      sweep_unit<T, NT, 7, RB>(a, it, u, r0, nr, vec, L.row, red);
+    else if (j == 8 || JMAX == 8)
+      sweep_unit<T, NT, 8, RB>(a, it, u, r0, nr, vec, L.row, red);
     else if (j <= 10)
       sweep_unit<T, NT, 10, RB>(a, it, u, r0, nr, vec, L.row, red);
+    else if (j == 11)
+      sweep_unit<T, NT, 11, RB>(a, it, u, r0, nr, vec, L.row, red);
     else
-      sweep_unit<T, NT, 16, RB>(a, it, u, r0, nr, vec, L.row, red);
+      sweep_unit<T, NT, 12, RB>(a, it, u, r0, nr, vec, L.row, red);
   }
   if (a.next && tid == 0) next_entry = atomicAdd(a.next, 1);
   if (a.x == nullptr || u.split >= 0) return;
@@ -1387,7 +1399,7 @@ size_t tucker_lds_bytes(const TuckMax& mx) {
 // them) and nrhs right-hand sides; false if a row is too long for it or its LDS beyond
 // mx.lds (the general kernels run the layout then).  A wavefront's lanes hold up to 4
 // slices of 64 packs in the kernels of 128 registers; longer rows take 8 or, with 512
-// threads, 16.  2 or 4 right-hand sides share a read of the factors where the row allows
+// threads, 12 (more spill).  2 or 4 right-hand sides share a read of the factors where the row allows
 // 4 slices.  The angular operands are staged in LDS while a CU still holds
 // kStageMinWaves wavefronts.
 //
@@ -1400,7 +1412,7 @@ bool stream_fits(const TuckMax& mx, int threads, int nrhs, bool dis, StreamFit* 
   for (; threads <= 512; threads *= 2) {
     const int nw = threads / 64, j = (mx.slices + nw - 1) / nw;
     const bool small = j <= 2 && nrhs == 1 && threads <= 256 && sizeof(T) == 4;
-    const int jmax = small ? 2 : (j <= 4 ? 4 : (j <= 8 ? 8 : (j <= 16 && threads == 512 ? 16 : 0)));
+    const int jmax = small ? 2 : (j <= 4 ? 4 : (j <= 8 ? 8 : (j <= 12 && threads == 512 ? 12 : 0)));
     if (!jmax) continue;
     for (int rb = jmax == 4 && nrhs > 1 ? (nrhs == 2 ? 2 : 4) : 1; rb >= 1; rb /= 2) {
       const size_t staged = StreamLds<T>(mx, nw, rb, true, dis).bytes();
@@ -1456,7 +1468,7 @@ hipError_t launch_stream(StreamArgs<T> a, const StreamFit& f, hipStream_t s) {
   TFMM_STREAM_CASE(512, 4, 2)
   TFMM_STREAM_CASE(512, 4, 4)
   TFMM_STREAM_CASE(512, 8, 1)
-  TFMM_STREAM_CASE(512, 16, 1)
+  TFMM_STREAM_CASE(512, 12, 1)
   return hipErrorInvalidValue;
 }
 
