@@ -15,8 +15,8 @@
 //            additions onto zero, one per polarisation, which commute exactly, so the
 //            result does not depend on which polarisation finishes first.
 // The sweep over the rows reads each factor once for both stages (the row-streaming kernels
-// below).  Rows too long for its registers run on the general kernels, one per stage, which
-// keep every vector in LDS.
+// below).  Layouts with rows too long for its registers run on the general kernel, which
+// reads the factors once per stage and keeps every vector in LDS.
 //
 // One-right-hand-side pass on an MI355X, before (one read of the factors per stage, angular
 // products on the vector units) and now: 4000 items of mean 15k elements, complex64, 231 and
@@ -40,13 +40,13 @@ using Real = float;
 
 namespace {
 
-// The general kernels' workgroup size.
+// The general kernel's workgroup size.
 constexpr int kGenThreads = 512;
 constexpr int kColPacks = 2;  // column packs per thread per chunk in the axpy stages
 // U^beta^T and the core are read once per call: the 256- and 512-thread kernels, which large
 // items take, load them non-temporally, so that these streams don't displace x, G, V and
 // the work tables in the caches (5-7% on boxes of 2 wavelengths and more; on small items it
-// cost 4%).
+// cost 4%).  The general kernel's loads:
 template <typename P>
 struct NtVec;
 template <>
@@ -57,16 +57,15 @@ template <>
 struct NtVec<double2> {
   typedef double v __attribute__((ext_vector_type(2)));
 };
-template <bool kNt, typename P>
+template <typename P>
 __device__ __forceinline__ P ldnt(const P* p) {
-  if (!kNt) return *p;
   const auto v = __builtin_nontemporal_load(reinterpret_cast<const typename NtVec<P>::v*>(p));
   P o;
   __builtin_memcpy(&o, &v, sizeof(P));
   return o;
 }
 
-// LDS regions of the general kernels (complex elements).
+// LDS regions of the general kernel (complex elements).
 // Aggregation:    r1 = x (n_beta), later t (r_theta r_phi);  r2 = y (r_beta), later
 //                 the angular intermediate.
 // Disaggregation: s1 = angular intermediate, S (r_theta r_phi), s (r_beta).
@@ -90,7 +89,7 @@ struct Lds {
 // S the smallest power of two >= npk, and each segment takes a row, four rows per
 // segment in flight, so a wavefront works on 4 * 64 / S rows at once instead of four
 // mostly idle ones; the segment's sum is a butterfly over its S lanes.
-template <typename T, bool kNt>
+template <typename T>
 __device__ __forceinline__ void wave_rowdots_short(const typename Tr<T>::c* rows, int ld, int first, int last,
                                                    int step, const typename Tr<T>::pack* vec, int npk,
                                                    typename Tr<T>::c* out, int lane) {
@@ -107,7 +106,7 @@ __device__ __forceinline__ void wave_rowdots_short(const typename Tr<T>::c* rows
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int b = first + step * (j0 + G * i + seg);
-      u[i] = (act && b < last) ? ldnt<kNt>(reinterpret_cast<const P*>(rows + (int64_t)b * ld) + sl) : pzero<P>();
+      u[i] = (act && b < last) ? ldnt(reinterpret_cast<const P*>(rows + (int64_t)b * ld) + sl) : pzero<P>();
     }
     C a[4];
 #pragma unroll
@@ -136,14 +135,14 @@ __device__ __forceinline__ void wave_rowdots_short(const typename Tr<T>::c* rows
 // wavefront per row.  Rows are 16-byte aligned with npk packs each; vec is an LDS
 // pack array.  Four rows at a time, two packs per row per iteration: eight 16-byte
 // loads in flight per lane.  Rows of at most 32 packs take the segmented form above.
-template <typename T, bool kNt>
+template <typename T>
 __device__ __forceinline__ void wave_rowdots(const typename Tr<T>::c* rows, int ld, int first, int last,
                                              int step, const typename Tr<T>::pack* vec, int npk,
                                              typename Tr<T>::c* out, int lane) {
   using C = typename Tr<T>::c;
   using P = typename Tr<T>::pack;
   if (npk <= 32) {
-    wave_rowdots_short<T, kNt>(rows, ld, first, last, step, vec, npk, out, lane);
+    wave_rowdots_short<T>(rows, ld, first, last, step, vec, npk, out, lane);
     return;
   }
   int b = first;
@@ -159,8 +158,8 @@ __device__ __forceinline__ void wave_rowdots(const typename Tr<T>::c* rows, int 
       P u[4], w[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        u[i] = ldnt<kNt>(r[i] + p);
-        w[i] = ldnt<kNt>(r[i] + p + 64);
+        u[i] = ldnt(r[i] + p);
+        w[i] = ldnt(r[i] + p + 64);
       }
       const P v0 = vec[p], v1 = vec[p + 64];
 #pragma unroll
@@ -172,7 +171,7 @@ __device__ __forceinline__ void wave_rowdots(const typename Tr<T>::c* rows, int 
     if (p < npk) {
       P u[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) u[i] = ldnt<kNt>(r[i] + p);
+      for (int i = 0; i < 4; ++i) u[i] = ldnt(r[i] + p);
       const P v0 = vec[p];
 #pragma unroll
       for (int i = 0; i < 4; ++i) pdot(a[i], u[i], v0);
@@ -189,11 +188,11 @@ __device__ __forceinline__ void wave_rowdots(const typename Tr<T>::c* rows, int 
     C a0 = czero<C>(), a1 = czero<C>();
     int p = lane;
     for (; p + 64 < npk; p += 128) {
-      const P u0 = ldnt<kNt>(r0 + p), u1 = ldnt<kNt>(r0 + p + 64);
+      const P u0 = ldnt(r0 + p), u1 = ldnt(r0 + p + 64);
       pdot(a0, u0, vec[p]);
       pdot(a1, u1, vec[p + 64]);
     }
-    if (p < npk) pdot(a0, ldnt<kNt>(r0 + p), vec[p]);
+    if (p < npk) pdot(a0, ldnt(r0 + p), vec[p]);
     a0.x += a1.x;
     a0.y += a1.y;
     a0 = wave_sum(a0);
@@ -201,64 +200,14 @@ __device__ __forceinline__ void wave_rowdots(const typename Tr<T>::c* rows, int 
   }
 }
 
-__device__ __forceinline__ float4 shfl_xor_pack(float4 v, int o) {
-  return make_float4(__shfl_xor(v.x, o, 64), __shfl_xor(v.y, o, 64), __shfl_xor(v.z, o, 64), __shfl_xor(v.w, o, 64));
-}
-__device__ __forceinline__ double2 shfl_xor_pack(double2 v, int o) {
-  return make_double2(__shfl_xor(v.x, o, 64), __shfl_xor(v.y, o, 64));
-}
-
-// One wavefront, at most 32 column packs: the lanes split into 64 / S groups of S
-// (S the smallest power of two >= npk); group g walks rows g, g + 64/S, ..., four in
-// flight, and the groups' partial sums meet in a butterfly.  acc[0] of lane p < npk
-// receives pack p (acc[1] is zero).
-template <typename T>
-__device__ __forceinline__ void wave_colaxpy_grouped(const typename Tr<T>::c* rows, int ld, int nrows,
-                                                     const typename Tr<T>::c* coef, int npk, int lane,
-                                                     typename Tr<T>::pack (&acc)[kColPacks]) {
-  using C = typename Tr<T>::c;
-  using P = typename Tr<T>::pack;
-  int S = 1;
-  while (S < npk) S <<= 1;
-  const int G = 64 / S;
-  const int g = lane / S, c = lane - g * S;
-  const bool in = c < npk;
-  P a = pzero<P>();
-  for (int b0 = g; b0 < nrows; b0 += 4 * G) {
-    P u[4];
-    C cf[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int b = b0 + G * i;
-      const bool ok = b < nrows;
-      u[i] = (in && ok) ? reinterpret_cast<const P*>(rows + (int64_t)b * ld)[c] : pzero<P>();
-      cf[i] = ok ? coef[b] : czero<C>();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) paxpy(a, u[i], cf[i]);
-  }
-  for (int o = S; o < 64; o <<= 1) a = padd(a, shfl_xor_pack(a, o));
-  acc[0] = a;
-#pragma unroll
-  for (int j = 1; j < kColPacks; ++j) acc[j] = pzero<P>();
-}
-
 // acc[j] (column packs base + tid + NT j) += sum_b rows[b][.] * coef[b];
-// four rows per iteration.  A single wavefront with at most 32 packs takes the
-// grouped form above (acc must then start at zero).
+// four rows per iteration.
 template <typename T, int NT>
 __device__ __forceinline__ void block_colaxpy(const typename Tr<T>::c* rows, int ld, int nrows,
                                               const typename Tr<T>::c* coef, int npk, int base, int tid,
                                               typename Tr<T>::pack (&acc)[kColPacks]) {
   using C = typename Tr<T>::c;
   using P = typename Tr<T>::pack;
-  constexpr bool kNt = NT >= 256;
-  if constexpr (NT == 64) {
-    if (base == 0 && npk <= 32) {
-      wave_colaxpy_grouped<T>(rows, ld, nrows, coef, npk, tid, acc);
-      return;
-    }
-  }
   const int p0 = base + tid;
   bool in[kColPacks];
 #pragma unroll
@@ -270,7 +219,7 @@ __device__ __forceinline__ void block_colaxpy(const typename Tr<T>::c* rows, int
     for (int i = 0; i < 4; ++i) {
       const P* r = reinterpret_cast<const P*>(rows + (int64_t)(b + i) * ld);
 #pragma unroll
-      for (int j = 0; j < kColPacks; ++j) u[i][j] = in[j] ? ldnt<kNt>(r + p0 + NT * j) : pzero<P>();
+      for (int j = 0; j < kColPacks; ++j) u[i][j] = in[j] ? ldnt(r + p0 + NT * j) : pzero<P>();
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -284,7 +233,7 @@ __device__ __forceinline__ void block_colaxpy(const typename Tr<T>::c* rows, int
     const C c = coef[b];
 #pragma unroll
     for (int j = 0; j < kColPacks; ++j)
-      if (in[j]) paxpy(acc[j], ldnt<kNt>(r + p0 + NT * j), c);
+      if (in[j]) paxpy(acc[j], ldnt(r + p0 + NT * j), c);
   }
 }
 
@@ -389,7 +338,7 @@ __device__ __forceinline__ void agg_stream(const typename Tr<T>::c* __restrict__
   __syncthreads();
 
   // y = U^beta^T x (rows b0 .. b1 - 1)
-  wave_rowdots<T, (NT >= 256)>(fac + it.off_ubt, it.ld_ub, b0 + wave, b1, (NT / 64), reinterpret_cast<const P*>(xs), nbp / E,
+  wave_rowdots<T>(fac + it.off_ubt, it.ld_ub, b0 + wave, b1, (NT / 64), reinterpret_cast<const P*>(xs), nbp / E,
                   ys, lane);
   __syncthreads();
 
@@ -596,7 +545,7 @@ __device__ __forceinline__ void dis_stream(const typename Tr<T>::c* __restrict__
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int Q = it.rt * it.rp;
   // s[b] = sum_q core[b][q] S[q]
-  wave_rowdots<T, (NT >= 256)>(fac + it.off_core, it.ld_c, b0 + wave, b1, (NT / 64), reinterpret_cast<const P*>(S2),
+  wave_rowdots<T>(fac + it.off_core, it.ld_c, b0 + wave, b1, (NT / 64), reinterpret_cast<const P*>(S2),
                   round_up(Q, E) / E, s3, lane);
   __syncthreads();
   // V[n] += conj(sum_b U^beta[n][b] s[b])
@@ -675,32 +624,26 @@ __device__ __forceinline__ void dis_unit(const typename Tr<T>::c* __restrict__ f
   dis_stream<T, NT>(fac, it, L, smem, nrhs, r, u.b0, u.b1, dst, V);
 }
 
-template <typename T, int NT>
-__global__ __launch_bounds__(NT) void tucker_agg_kernel(const typename Tr<T>::c* __restrict__ fac,
-                                                        const TuckWork* __restrict__ work,
-                                                        const TuckSplit* __restrict__ splits, TuckMax mx, int n_theta,
-                                                        int n_phi, int nrhs,
-                                                        const typename Tr<T>::c* __restrict__ x,
-                                                        typename Tr<T>::c* __restrict__ F, typename Tr<T>::c* part,
-                                                        int64_t part_stride) {
+// The general kernel: a unit's aggregation (x given), its disaggregation (G given), or with
+// both a workgroup for each, neighbours in the launch, so that the few long items whose time a
+// layout waits for run both at once.  Workgroups go to the eight XCDs round-robin: every other
+// group of four pairs is swapped, so that no XCD runs one stage only.  (100 groups of mean 909
+// and one of 17000 basis functions, complex64, a pass: 719 us; 1356 with a launch a stage.)
+template <typename T>
+__global__ __launch_bounds__(kGenThreads) void tucker_general_kernel(
+    const typename Tr<T>::c* __restrict__ fac, const TuckWork* __restrict__ work, const TuckSplit* __restrict__ splits,
+    TuckMax mx, int n_theta, int n_phi, int nrhs, const typename Tr<T>::c* __restrict__ x,
+    typename Tr<T>::c* __restrict__ F, const typename Tr<T>::c* __restrict__ G, typename Tr<T>::c* __restrict__ V,
+    typename Tr<T>::c* part, int64_t part_stride) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const TuckWork w = work[blockIdx.x];
-  agg_unit<T, NT>(fac, w, splits, Lds<T>(mx), smem, n_theta, n_phi, nrhs, blockIdx.y, x, F,
-                  part, part_stride);
-}
-
-template <typename T, int NT>
-__global__ __launch_bounds__(NT) void tucker_dis_kernel(const typename Tr<T>::c* __restrict__ fac,
-                                                        const TuckWork* __restrict__ work,
-                                                        const TuckSplit* __restrict__ splits, TuckMax mx, int n_theta,
-                                                        int n_phi, int nrhs,
-                                                        const typename Tr<T>::c* __restrict__ G,
-                                                        typename Tr<T>::c* __restrict__ V, typename Tr<T>::c* part,
-                                                        int64_t part_stride) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  const TuckWork w = work[blockIdx.x];
-  dis_unit<T, NT>(fac, w, splits, Lds<T>(mx), smem, n_theta, n_phi, nrhs, blockIdx.y, G, V,
-                  part, part_stride);
+  const bool pass = x != nullptr && G != nullptr;
+  const int i = blockIdx.x;
+  const bool dis = pass ? ((i ^ (i >> 3)) & 1) != 0 : x == nullptr;
+  const TuckWork w = work[pass ? i >> 1 : i];
+  if (dis)
+    dis_unit<T, kGenThreads>(fac, w, splits, Lds<T>(mx), smem, n_theta, n_phi, nrhs, blockIdx.y, G, V, part, part_stride);
+  else
+    agg_unit<T, kGenThreads>(fac, w, splits, Lds<T>(mx), smem, n_theta, n_phi, nrhs, blockIdx.y, x, F, part, part_stride);
 }
 
 // ------------------------------------------------------------ row-streaming kernels
@@ -1389,7 +1332,7 @@ hipError_t launch_zero_rows(size_t elem_bytes, void* base, const int32_t* rows, 
     return launch_stream_kernel<T, NT, JMAX, RB>(a, f, entries, s); \
   }
 
-// The general kernels' LDS.
+// The general kernel's LDS.
 template <typename T>
 size_t tucker_lds_bytes(const TuckMax& mx) {
   return Lds<T>(mx).bytes();
@@ -1397,7 +1340,7 @@ size_t tucker_lds_bytes(const TuckMax& mx) {
 
 // The row-streaming kernel for workgroups of `threads` (more where the longest row needs
 // them) and nrhs right-hand sides; false if a row is too long for it or its LDS beyond
-// mx.lds (the general kernels run the layout then).  A wavefront's lanes hold up to 4
+// mx.lds (the general kernel runs the layout then).  A wavefront's lanes hold up to 4
 // slices of 64 packs in the kernels of 128 registers; longer rows take 8 or, with 512
 // threads, 12 (more spill).  2 or 4 right-hand sides share a read of the factors where the row allows
 // 4 slices.  The angular operands are staged in LDS while a CU still holds
@@ -1524,14 +1467,12 @@ hipError_t launch_units(const TuckPlan& pl, int threads, int n_theta, int n_phi,
     a.next = persistent ? pl.next : nullptr;
     e = launch_stream<T>(a, f, s);
   } else {
-    if (x)
-      hipLaunchKernelGGL((tucker_agg_kernel<T, kGenThreads>), dim3(pl.n_units, nrhs), dim3(kGenThreads),
-                         Lds<T>(pl.mx).agg_bytes(), s, static_cast<const C*>(pl.factors), pl.work, pl.splits, pl.mx, n_theta, n_phi, nrhs, static_cast<const C*>(x), static_cast<C*>(F),
-                         static_cast<C*>(pl.part), pl.part_stride);
-    if (G)
-      hipLaunchKernelGGL((tucker_dis_kernel<T, kGenThreads>), dim3(pl.n_units, nrhs), dim3(kGenThreads),
-                         Lds<T>(pl.mx).dis_bytes(), s, static_cast<const C*>(pl.factors), pl.work, pl.splits, pl.mx, n_theta, n_phi, nrhs, static_cast<const C*>(G), static_cast<C*>(V),
-                         static_cast<C*>(pl.part), pl.part_stride);
+    const Lds<T> L(pl.mx);
+    hipLaunchKernelGGL((tucker_general_kernel<T>), dim3((unsigned)pl.n_units * (x && G ? 2 : 1), nrhs),
+                       dim3(kGenThreads), x && G ? L.bytes() : (x ? L.agg_bytes() : L.dis_bytes()), s,
+                       static_cast<const C*>(pl.factors), pl.work, pl.splits, pl.mx, n_theta, n_phi, nrhs,
+                       static_cast<const C*>(x), static_cast<C*>(F), static_cast<const C*>(G), static_cast<C*>(V),
+                       static_cast<C*>(pl.part), pl.part_stride);
     e = hipGetLastError();
   }
   if (e != hipSuccess) return e;

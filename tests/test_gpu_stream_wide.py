@@ -3,8 +3,8 @@ blocks.
 
 A row of U^beta^T and the core is cut into slices of 64 packs (128 complex64 or 64 complex128
 values); the wavefronts of a workgroup share them.  The layouts hold an item for every number
-of slices a wavefront from 1 to the largest of a kernel (4, 8, or 12 with 512 threads), its last
-slice partly filled.  `split` cuts the items into row blocks whose partial sums are added
+of slices a wavefront from 1 to the largest of a kernel (4, 8, or 12 with 512 threads; with 13 the
+general kernel runs the layout), its last slice partly filled.  `split` cuts the items into row blocks whose partial sums are added
 afterwards.  Bounds: FP32 sums of at most 2e4 products of O(1 / sqrt(K)) terms in four
 contractions within 1e-5 of the oracle, FP64 within 1e-11.  A pass equals its stages bit for bit.
 """
@@ -39,7 +39,7 @@ def _slices(prec, nb, q):
 
 
 @pytest.mark.parametrize("prec", [T.FMM_C128, T.FMM_C64], ids=["c128", "c64"])
-@pytest.mark.parametrize("threads,most", [(64, 4), (64, 8), (128, 4), (128, 8), (256, 8), (512, 4), (512, 8), (512, 12)])
+@pytest.mark.parametrize("threads,most", [(64, 4), (64, 8), (128, 4), (128, 8), (256, 8), (512, 4), (512, 8), (512, 12), (512, 13)])
 @pytest.mark.parametrize("split", [False, True])
 def test_slices_per_wavefront(prec, threads, most, split, monkeypatch):
     if split:
