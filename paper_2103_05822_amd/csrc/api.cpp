@@ -344,24 +344,28 @@ fmm_status route_of(const PrecSlot& s, fmm_prec prec, int nrhs, Route* r) {
   return FMM_OK;
 }
 
-// Drops a captured graph (it may point at tables or factors about to change).
-void drop_graph(fmm_tucker_t h);
-
 // Work counter of the pass kernel (allocated once) and partial-sum buffer of the split
-// items for nrhs right-hand sides (grown on demand; a graph captured with the old
-// buffer is dropped).
-fmm_status ensure_part(fmm_tucker_t h, PrecSlot& s, fmm_prec prec, int nrhs) {
+// items for nrhs right-hand sides (grown on demand).  Captured graphs, the handle's or a
+// caller's own, keep the addresses of their capture: a buffer that became too small stays
+// until the handle's end.  Each is at least twice the one before, so that all of them
+// together are less than twice the last.
+fmm_status ensure_part(PrecSlot& s, fmm_prec prec, int nrhs) {
   if (!s.next) TFMM_HIP(hipMalloc(&s.next, 256));
   s.plan.next = s.next;
   if (s.plan.n_splits == 0) return FMM_OK;
   const size_t need = (size_t)s.plan.part_stride * nrhs * elem_bytes(prec);
   if (need > s.part_bytes) {
-    drop_graph(h);
-    if (s.part) (void)hipFree(s.part);
-    s.part = nullptr;
-    s.part_bytes = 0;
-    TFMM_HIP(hipMalloc(&s.part, need));
-    s.part_bytes = need;
+    size_t bytes = std::max(need, 2 * s.part_bytes);
+    void* p = nullptr;
+    if (bytes > need && hipMalloc(&p, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      p = nullptr;
+      bytes = need;
+    }
+    if (!p) TFMM_HIP(hipMalloc(&p, bytes));
+    if (s.part) s.old_parts.push_back(s.part);
+    s.part = p;
+    s.part_bytes = bytes;
   }
   s.plan.part = s.part;
   return FMM_OK;
@@ -369,9 +373,11 @@ fmm_status ensure_part(fmm_tucker_t h, PrecSlot& s, fmm_prec prec, int nrhs) {
 
 void part_release(PrecSlot& s) {
   if (s.part) (void)hipFree(s.part);
+  for (void* p : s.old_parts) (void)hipFree(p);
   if (s.next) (void)hipFree(s.next);
   s.part = nullptr;
   s.part_bytes = 0;
+  s.old_parts.clear();
   s.next = nullptr;
   s.plan.part = nullptr;
   s.plan.next = nullptr;
@@ -395,7 +401,7 @@ fmm_status run_stage(fmm_tucker_t h, PrecSlot& s, fmm_prec prec, int nrhs, int s
     if ((st = mrhs_get(s, elem_bytes(prec), L, nrhs, r.tile_steps, r.rhs_chunk, r.order, &mp)) != FMM_OK) return st;
     return mrhs_run(*mp, s, r.variant, elem_bytes(prec), stage, x, F, G, V, hs);
   }
-  if ((st = ensure_part(h, s, prec, nrhs)) != FMM_OK) return st;
+  if ((st = ensure_part(s, prec, nrhs)) != FMM_OK) return st;
   if (prec == FMM_C128) {
     if ((st = lds_check(tucker_lds_bytes<double>(s.plan.mx))) != FMM_OK) return st;
     if (stage == 0) TFMM_HIP(launch_tucker_agg<double>(s.plan, r.threads, L.n_theta, L.n_phi, nrhs, x, F, hs));
@@ -410,6 +416,7 @@ fmm_status run_stage(fmm_tucker_t h, PrecSlot& s, fmm_prec prec, int nrhs, int s
   return FMM_OK;
 }
 
+// Drops a captured graph (it may point at tables or factors about to change).
 void drop_graph(fmm_tucker_t h) {
   if (h->graph_exec) (void)hipGraphExecDestroy(h->graph_exec);
   if (h->graph) (void)hipGraphDestroy(h->graph);
@@ -798,7 +805,7 @@ extern "C" fmm_status fmm_graph_capture(fmm_tucker_t h, fmm_prec prec, int32_t n
     MrhsPlan* mp = nullptr;
     if ((st = mrhs_get(*s, elem_bytes(prec), h->layout, nrhs, r.tile_steps, r.rhs_chunk, r.order, &mp)) != FMM_OK)
       return st;
-  } else if ((st = ensure_part(h, *s, prec, nrhs)) != FMM_OK) {
+  } else if ((st = ensure_part(*s, prec, nrhs)) != FMM_OK) {
     return st;
   }
   TFMM_HIP(hipStreamBeginCapture(hs, hipStreamCaptureModeThreadLocal));

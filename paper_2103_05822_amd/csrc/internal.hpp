@@ -95,6 +95,7 @@ struct PrecSlot {
   std::vector<TuneChoice> tuned;
   void* part = nullptr;             // library-owned partial sums of split items (device)
   size_t part_bytes = 0;
+  std::vector<void*> old_parts;     // smaller buffers before it, which captured graphs may use
   int32_t* next = nullptr;          // library-owned work counter of the pass kernel (device)
 };
 
