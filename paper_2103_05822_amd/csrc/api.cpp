@@ -327,7 +327,7 @@ fmm_status route_of(const PrecSlot& s, fmm_prec prec, int nrhs, Route* r) {
     r->mfma = true;
     r->variant = prec == FMM_BF16X2 ? 1 : 2;
   } else {
-    r->mfma = nrhs % 2 == 0 && nrhs >= kMfmaMinRhs;
+    r->mfma = nrhs % 2 == 0 && (nrhs >= kMfmaMinRhs || !s.streams);
     r->variant = prec == FMM_C128 ? 3 : 0;
   }
   for (const TuneChoice& t : s.tuned)
