@@ -839,7 +839,7 @@ template <typename T, int NT, int J, int RB>
 __device__ __forceinline__ void sweep_rows(const typename Tr<T>::pack* ub, const typename Tr<T>::pack* cb, int npu,
                                            int npc, int b0, int b1,
                                            const typename Tr<T>::pack* vec, int vrow, T* red, int wave, int lane,
-                                           typename Tr<T>::pack (&acc)[RB][J]) {
+                                           bool agg, bool dis, typename Tr<T>::pack (&acc)[RB][J]) {
   using C = typename Tr<T>::c;
   using P = typename Tr<T>::pack;
   constexpr int NW = NT / 64;
@@ -881,6 +881,12 @@ __device__ __forceinline__ void sweep_rows(const typename Tr<T>::pack* ub, const
   int jc = 0;
 #pragma unroll
   for (int j = 0; j < J; ++j) jc += isu[j] ? 1 : 0;
+  // A stage alone needs only the dot products with its vector and only its own sums.  Several
+  // right-hand sides leave the absent stage's out, per wavefront (300 items of mean 58k elements,
+  // complex64, 256 threads, the two stages with 3 and 5: 321 and 460 us, now 284 and 413); for one
+  // the branches cost more than the products (4 wavelengths: both stages 1490 us, 1874 with them).
+  const bool dots = RB == 1 || (agg && jc > 0) || (dis && jc < J);
+  const bool sums = RB == 1 || (agg && jc < J) || (dis && jc > 0);
   P xv[kVecRegs ? J : 1];
   if constexpr (kVecRegs) {
 #pragma unroll
@@ -902,45 +908,48 @@ __device__ __forceinline__ void sweep_rows(const typename Tr<T>::pack* ub, const
   };
   int par = 0;
   auto step = [&](const P (&u)[KR][J], int b) {
-    C d[KR][RB][2];  // dot products of the row with x (U_b) and S (core_b)
+    T tot = T(0);
+    if (dots) {
+      C d[KR][RB][2];  // dot products of the row with x (U_b) and S (core_b)
 #pragma unroll
-    for (int k = 0; k < KR; ++k)
+      for (int k = 0; k < KR; ++k)
 #pragma unroll
-      for (int r = 0; r < RB; ++r) d[k][r][0] = d[k][r][1] = czero<C>();
+        for (int r = 0; r < RB; ++r) d[k][r][0] = d[k][r][1] = czero<C>();
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-      P xr[RB];
+      for (int j = 0; j < J; ++j) {
+        P xr[RB];
 #pragma unroll
-      for (int r = 0; r < RB; ++r) {
-        if constexpr (kVecRegs) {
-          xr[r] = xv[j];
-        } else {
-          xr[r] = pkeep(vec[r * vrow + voff[j]], live[j]);
+        for (int r = 0; r < RB; ++r) {
+          if constexpr (kVecRegs) {
+            xr[r] = xv[j];
+          } else {
+            xr[r] = pkeep(vec[r * vrow + voff[j]], live[j]);
+          }
         }
+#pragma unroll
+        for (int k = 0; k < KR; ++k)
+#pragma unroll
+          for (int r = 0; r < RB; ++r) {
+            if (j > 0) restart(d[k][r], j == jc);  // U_b's sum up to slice jc, then core_b's
+            pdot(d[k][r][1], u[k][j], xr[r]);
+          }
       }
 #pragma unroll
       for (int k = 0; k < KR; ++k)
 #pragma unroll
-        for (int r = 0; r < RB; ++r) {
-          if (j > 0) restart(d[k][r], j == jc);  // U_b's sum up to slice jc, then core_b's
-          pdot(d[k][r][1], u[k][j], xr[r]);
-        }
+        for (int r = 0; r < RB; ++r) restart(d[k][r], jc == J);
+      T v[NV];
+#pragma unroll
+      for (int k = 0; k < KR; ++k)
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+          for (int m = 0; m < 2; ++m) {
+            v[((k * RB + r) * 2 + m) * 2] = d[k][r][m].x;
+            v[((k * RB + r) * 2 + m) * 2 + 1] = d[k][r][m].y;
+          }
+      tot = wave_fold<NV, 32>(v, lane);
     }
-#pragma unroll
-    for (int k = 0; k < KR; ++k)
-#pragma unroll
-      for (int r = 0; r < RB; ++r) restart(d[k][r], jc == J);
-    T v[NV];
-#pragma unroll
-    for (int k = 0; k < KR; ++k)
-#pragma unroll
-      for (int r = 0; r < RB; ++r)
-#pragma unroll
-        for (int m = 0; m < 2; ++m) {
-          v[((k * RB + r) * 2 + m) * 2] = d[k][r][m].x;
-          v[((k * RB + r) * 2 + m) * 2 + 1] = d[k][r][m].y;
-        }
-    T tot = wave_fold<NV, 32>(v, lane);
     constexpr int kSpan = 64 / NV;  // lanes per value
     int stride = kSpan;
     if constexpr (NW > 1) {
@@ -958,6 +967,7 @@ __device__ __forceinline__ void sweep_rows(const typename Tr<T>::pack* ub, const
       tot = high_add<NV>(tot);
       stride = 1;
     }
+    if (!sums) return;
 #pragma unroll
     for (int k = 0; k < KR; ++k) {
       const bool in = b + k < b1;
@@ -1028,7 +1038,7 @@ __device__ __forceinline__ void sweep_unit(const StreamArgs<T>& a, const TuckIte
   P acc[RB][J];
   sweep_rows<T, NT, J, RB>(reinterpret_cast<const P*>(a.fac + it.off_ubt),
                            reinterpret_cast<const P*>(a.fac + it.off_core), npu, npc, u.b0, u.b1,
-                           reinterpret_cast<const P*>(vec), vrow / E, red, wave, lane, acc);
+                           reinterpret_cast<const P*>(vec), vrow / E, red, wave, lane, agg, dis, acc);
 #pragma unroll
   for (int j = 0; j < J; ++j) {
     const int s = wave + NW * j;
@@ -1071,9 +1081,9 @@ __device__ __forceinline__ TuckWork const_load(const TuckWork* p) {
   return __builtin_bit_cast(TuckWork, v);
 }
 
-// One work entry: unit iu and block blk of at most RB right-hand sides.  The entries of a
-// unit follow each other, so that the second and later blocks find the factors in the
-// memory-side cache.
+// One work entry: unit iu and block blk of at most RB right-hand sides.  In a pass, and in a
+// stage without split items, the entries of a unit follow each other, so that the second and
+// later blocks find the factors in the memory-side cache.
 template <typename T, int NT, int JMAX, int RB>
 __device__ __forceinline__ void stream_entry(const StreamArgs<T>& a, const StreamLds<T>& L, unsigned char* smem,
                                              int iu, int blk, int32_t& next_entry) {
@@ -1186,7 +1196,9 @@ void tucker_pass_kernel(StreamArgs<T> a) {
   const int total = a.n_units * a.n_rblk;
   if (a.next == nullptr) {
     int32_t none;
-    stream_entry<T, NT, JMAX, RB>(a, L, smem, blockIdx.x, blockIdx.y, none);
+    const int iu = gridDim.y == 1 ? blockIdx.x / a.n_rblk : blockIdx.x;
+    const int blk = gridDim.y == 1 ? blockIdx.x - iu * a.n_rblk : blockIdx.y;
+    stream_entry<T, NT, JMAX, RB>(a, L, smem, iu, blk, none);
     return;
   }
   int32_t mine = 0;  // (first thread) the next entry, taken when the current one's sweep is done
@@ -1375,7 +1387,12 @@ bool stream_fits(const TuckMax& mx, int threads, int nrhs, bool dis, StreamFit* 
 
 template <typename T, int NT, int JMAX, int RB>
 hipError_t launch_stream_kernel(const StreamArgs<T>& a, const StreamFit& f, int64_t entries, hipStream_t s) {
-  dim3 grid((unsigned)a.n_units, (unsigned)a.n_rblk);
+  // A stage: the column blocks of a unit follow each other (see stream_entry; 140 items of mean
+  // 1.7M elements, complex64, the two stages with 3 right-hand sides: 2420 us in the other order,
+  // now 2180).  Split items go by columns first: their units are alike, and 20 groups of 2
+  // wavelengths took 5% less so.
+  const bool flat = a.splits == nullptr && entries <= (1 << 22);
+  dim3 grid((unsigned)(flat ? entries : a.n_units), (unsigned)(flat ? 1 : a.n_rblk));
   if (a.next) {
     const hipError_t e = persistent_grid(&tucker_pass_kernel<T, NT, JMAX, RB>, NT, f.lds, entries, &grid.x);
     if (e != hipSuccess) return e;
