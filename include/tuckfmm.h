@@ -63,9 +63,13 @@ typedef enum {
  *              down to order 2^-16 (FP32-level error).  Needs an even nrhs.
  *
  * Kernels.  The streaming kernels run one workgroup per (group, polarisation) and block of
- * up to four right-hand sides and sweep the rows of its factors once: a pass reads them
- * once for both stages.  They take 64, 128, 256 or 512 threads by the mean item size, or as
- * tuned (the environment variable TUCKFMM_STREAM_THREADS, read at upload, fixes the
+ * right-hand sides and sweep the rows of its factors once: a pass reads them once for both
+ * stages.  A block holds two right-hand sides, for some counts four, where the longest row
+ * of U^beta and the core together takes at most 32 slices of 128 complex64 or 64 complex128
+ * values and the layout has units enough, else one; layouts with rows of more than 96 slices
+ * run a kernel that reads the factors once per stage and right-hand side.  They take 64,
+ * 128, 256 or 512 threads by the mean item size, the longest row and nrhs, or as tuned (the
+ * environment variable TUCKFMM_STREAM_THREADS, read at upload, fixes the
  * default; rows too long for the size chosen take more).  Untuned, FMM_C128 and FMM_C64 run
  * them for an odd nrhs and for 2 and 4, and the matrix-core products (FP64 and FP32 MFMA)
  * for an even nrhs from 6; fmm_tucker_tune may choose differently for an nrhs (it offers

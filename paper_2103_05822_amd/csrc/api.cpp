@@ -319,7 +319,7 @@ bool mfma_allows(fmm_prec prec, int nrhs) { return !prec_is_split(prec) || nrhs 
 
 fmm_status route_of(const PrecSlot& s, fmm_prec prec, int nrhs, Route* r) {
   *r = Route{};
-  r->threads = nrhs == 1 ? s.threads : s.threads_multi;
+  r->threads = nrhs == 1 || s.fixed_threads ? s.threads : multi_threads(s.plan.mx, s.plan.n_units, s.threads, nrhs);
   for (const TuneChoice& t : s.tuned)
     if (t.nrhs == nrhs && t.path == 0 && t.threads) r->threads = t.threads;
   if (prec_is_split(prec)) {
@@ -672,16 +672,17 @@ extern "C" fmm_status fmm_tucker_upload(fmm_tucker_t h, fmm_prec prec, void* are
     P.mx.stage = 1;
     if (const char* env = std::getenv("TUCKFMM_STAGE_ANGULAR")) P.mx.stage = std::atoi(env) != 0;
     StreamFit f{};
-    const bool fits = prec == FMM_C128 ? stream_fits<double>(P.mx, t_staged, 1, true, &f)
-                                       : stream_fits<float>(P.mx, t_staged, 1, true, &f);
+    const int n_units = (int)P.units.size();
+    const bool fits = prec == FMM_C128 ? stream_fits<double>(P.mx, n_units, t_staged, 1, true, &f)
+                                       : stream_fits<float>(P.mx, n_units, t_staged, 1, true, &f);
     sl.threads = fits && f.staged ? t_staged : t_plain;
-    // several right-hand sides leave fewer wavefronts per CU: smaller workgroups keep more
-    // units in flight (140k elements, 3 and 5 right-hand sides, complex64: 230 and 347 us
-    // with 128 threads, 252 and 426 with 512; complex128: 484 and 740 against 444 and 693)
-    sl.threads_multi = prec != FMM_C128 && c < 2e5 ? 128 : sl.threads;
+    sl.fixed_threads = false;
     if (const char* env = std::getenv("TUCKFMM_STREAM_THREADS")) {
       const int v = std::atoi(env);
-      if (v == 64 || v == 128 || v == 256 || v == 512) sl.threads = sl.threads_multi = v;
+      if (v == 64 || v == 128 || v == 256 || v == 512) {
+        sl.threads = v;
+        sl.fixed_threads = true;
+      }
     }
   }
   sl.streams = (prec == FMM_C128 ? tucker_lds_bytes<double>(P.mx) : tucker_lds_bytes<float>(P.mx)) <=

@@ -88,8 +88,8 @@ struct PrecSlot {
   int device = -1;
   TuckPlan plan;          // device pointers into the arena
   std::vector<TuckItem> items;      // host copy of the item table
-  int threads = 512;                // default workgroup size of the streaming kernels
-  int threads_multi = 512;          // the same with several right-hand sides
+  int threads = 512;                // workgroup size of the streaming kernels for one right-hand side
+  bool fixed_threads = false;       // the same for several (else see multi_threads)
   bool streams = true;              // the streaming kernels' LDS fits the largest item
   std::list<MrhsPlan> mrhs;         // built on first use per (nrhs, knobs); stable addresses
   std::vector<TuneChoice> tuned;

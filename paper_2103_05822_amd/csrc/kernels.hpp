@@ -6,8 +6,8 @@
 
 namespace tuckfmm {
 
-// Tucker aggregation / disaggregation / whole pass over an uploaded plan, one
-// workgroup of `threads` (64, 128, 256 or 512) per item and right-hand side.
+// Tucker aggregation / disaggregation / whole pass over an uploaded plan, in workgroups of
+// `threads` (64, 128, 256 or 512; more where a row needs them).
 template <typename T>
 hipError_t launch_tucker_agg(const TuckPlan& pl, int threads, int n_theta, int n_phi, int nrhs, const void* x,
                              void* F, hipStream_t s);
@@ -36,7 +36,9 @@ struct StreamFit {
   size_t lds;
 };
 template <typename T>
-bool stream_fits(const TuckMax& mx, int threads, int nrhs, bool dis, StreamFit* out);
+bool stream_fits(const TuckMax& mx, int n_units, int threads, int nrhs, bool dis, StreamFit* out);
+// Workgroup size for nrhs > 1 right-hand sides, `threads` that for one.
+int multi_threads(const TuckMax& mx, int n_units, int threads, int nrhs);
 
 // Grouped complex GEMM of the multi-RHS path (variant 0: FP32 MFMA, 1: BF16 two-piece
 // split, 2: BF16 three-piece split, all on complex64 data with FP32 accumulation;

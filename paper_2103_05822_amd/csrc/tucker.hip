@@ -1350,26 +1350,47 @@ size_t tucker_lds_bytes(const TuckMax& mx) {
   return Lds<T>(mx).bytes();
 }
 
+// Whether work entries of two right-hand sides each, in workgroups of `threads`, still hold a
+// workgroup of 512 threads per CU.  Below that (layouts of few units) sharing a read of the
+// factors leaves CUs idle, and every right-hand side is an entry of its own: 100 groups of 2
+// wavelengths, complex64, 2 right-hand sides, a pass and the two stages, 169 and 368 us, shared
+// 237 and 415; 8 groups of 240 basis functions 33 and 50, shared 48 and 53; with 3 of them the
+// 100 groups have enough entries: 205 and 475, shared 241 and 427.
+constexpr int64_t kFillThreads = 256 * 512;
+static bool entries_fill(int n_units, int nrhs, int threads) {
+  return (int64_t)n_units * ((nrhs + 1) / 2) * threads >= kFillThreads;
+}
+
+static int slices_per_wave(const TuckMax& mx, int threads) { return (mx.slices + threads / 64 - 1) / (threads / 64); }
+
 // The row-streaming kernel for workgroups of `threads` (more where the longest row needs
 // them) and nrhs right-hand sides; false if a row is too long for it or its LDS beyond
 // mx.lds (the general kernel runs the layout then).  A wavefront's lanes hold up to 4
 // slices of 64 packs in the kernels of 128 registers; longer rows take 8 or, with 512
-// threads, 12 (more spill).  2 or 4 right-hand sides share a read of the factors where the row allows
-// 4 slices.  The angular operands are staged in LDS while a CU still holds
-// kStageMinWaves wavefronts.
+// threads, 12 (more spill).  Two right-hand sides share a read of the factors where the row
+// allows 4 slices and the entries fill the chip.  Four lose to two (1.5 wavelengths, 160
+// groups, complex64, 5 right-hand sides, a pass and the stages: 289 and 534 us with two, 397 and
+// 543 with four), but for 3 or a multiple of 4 where 512 threads hold at most 3 slices and two
+// entries a CU are left (3 right-hand sides: 1 wavelength, 300 groups, complex128, 394 and 667
+// with two, 371 and 609 with four; 2 wavelengths, complex64, 256 groups 596 and 1040, 558 and
+// 991; 100 groups 241 and 427, 394 and 700).  The angular operands are staged in LDS while a CU
+// still holds kStageMinWaves wavefronts.
 //
 // Small complex64 items are bound by the latency of each unit's phases, which more workgroups
 // on a CU hide.  With at most 2 slices the kernel fits 96 registers, so 5 wavefronts a SIMD
 // (4000 items of mean 15k: 135 us with 4, 126 with 5; 6 spill, 134).  With 512
 // threads 5 a SIMD hold no more workgroups than 4; in complex128 it was not tried.
 template <typename T>
-bool stream_fits(const TuckMax& mx, int threads, int nrhs, bool dis, StreamFit* out) {
+bool stream_fits(const TuckMax& mx, int n_units, int threads, int nrhs, bool dis, StreamFit* out) {
   for (; threads <= 512; threads *= 2) {
-    const int nw = threads / 64, j = (mx.slices + nw - 1) / nw;
+    const int nw = threads / 64, j = slices_per_wave(mx, threads);
     const bool small = j <= 2 && nrhs == 1 && threads <= 256 && sizeof(T) == 4;
     const int jmax = small ? 2 : (j <= 4 ? 4 : (j <= 8 ? 8 : (j <= 12 && threads == 512 ? 12 : 0)));
     if (!jmax) continue;
-    for (int rb = jmax == 4 && nrhs > 1 ? (nrhs == 2 ? 2 : 4) : 1; rb >= 1; rb /= 2) {
+    int most = 1;
+    if (jmax == 4 && nrhs > 1 && entries_fill(n_units, nrhs, threads))
+      most = threads == 512 && j <= 3 && (nrhs + 1) % 4 < 2 && (int64_t)n_units * ((nrhs + 3) / 4) >= 512 ? 4 : 2;
+    for (int rb = most; rb >= 1; rb /= 2) {
       const size_t staged = StreamLds<T>(mx, nw, rb, true, dis).bytes();
       const size_t plain = StreamLds<T>(mx, nw, rb, false, dis).bytes();
       if (plain + kPassStaticLds > (size_t)mx.lds) continue;
@@ -1384,6 +1405,27 @@ bool stream_fits(const TuckMax& mx, int threads, int nrhs, bool dis, StreamFit* 
   }
   return false;
 }
+
+#ifndef TUCKFMM_STREAM_F64
+// The smallest workgroups of at least 128 threads whose wavefronts hold the longest row in 4
+// slices, so that right-hand sides share reads and many units are in flight (160 groups of 1.5
+// wavelengths, complex64, 5 right-hand sides, a pass and the stages: 289 and 534 us with 256
+// threads, 373 and 595 with 512; with 128, which hold 7 slices and share nothing, 349 and 573).
+// Two right-hand sides are one read either way and prefer 3 slices (1.5 wavelengths: 137 and 233
+// with 512 threads, 181 and 323 with 256, 4 slices; 1 wavelength, 1000 groups: 269 and 421 with
+// 256, 424 and 533 with 512).  Where the entries don't fill the chip, up to the size for one.
+int multi_threads(const TuckMax& mx, int n_units, int threads, int nrhs) {
+  const int most = nrhs == 2 ? 3 : 4;
+  int t = 128;
+  while (t < 512 && slices_per_wave(mx, t) > most) t *= 2;
+  if (slices_per_wave(mx, t) > 4) return threads;
+  for (; t <= 512; t *= 2) {
+    if (entries_fill(n_units, nrhs, t)) return t;
+    if (t >= threads) break;
+  }
+  return threads;
+}
+#endif
 
 template <typename T, int NT, int JMAX, int RB>
 hipError_t launch_stream_kernel(const StreamArgs<T>& a, const StreamFit& f, int64_t entries, hipStream_t s) {
@@ -1414,15 +1456,12 @@ hipError_t launch_stream(StreamArgs<T> a, const StreamFit& f, hipStream_t s) {
   }
   TFMM_STREAM_CASE(64, 4, 1)
   TFMM_STREAM_CASE(64, 4, 2)
-  TFMM_STREAM_CASE(64, 4, 4)
   TFMM_STREAM_CASE(64, 8, 1)
   TFMM_STREAM_CASE(128, 4, 1)
   TFMM_STREAM_CASE(128, 4, 2)
-  TFMM_STREAM_CASE(128, 4, 4)
   TFMM_STREAM_CASE(128, 8, 1)
   TFMM_STREAM_CASE(256, 4, 1)
   TFMM_STREAM_CASE(256, 4, 2)
-  TFMM_STREAM_CASE(256, 4, 4)
   TFMM_STREAM_CASE(256, 8, 1)
   TFMM_STREAM_CASE(512, 4, 1)
   TFMM_STREAM_CASE(512, 4, 2)
@@ -1461,8 +1500,8 @@ hipError_t launch_units(const TuckPlan& pl, int threads, int n_theta, int n_phi,
   StreamFit f;
   // a layout that fits one of the calls in full takes it in all of them, so that a pass
   // equals its stages
-  if (stream_fits<T>(pl.mx, threads, nrhs, true, &f)) {
-    if (!G) stream_fits<T>(pl.mx, threads, nrhs, false, &f);
+  if (stream_fits<T>(pl.mx, pl.n_units, threads, nrhs, true, &f)) {
+    if (!G) stream_fits<T>(pl.mx, pl.n_units, threads, nrhs, false, &f);
     StreamArgs<T> a;
     a.fac = static_cast<const C*>(pl.factors);
     a.work = pl.work;
@@ -1515,7 +1554,7 @@ hipError_t launch_tucker_pass(const TuckPlan& pl, int threads, int n_theta, int 
 }
 
 template size_t tucker_lds_bytes<Real>(const TuckMax&);
-template bool stream_fits<Real>(const TuckMax&, int, int, bool, StreamFit*);
+template bool stream_fits<Real>(const TuckMax&, int, int, int, bool, StreamFit*);
 template hipError_t launch_tucker_agg<Real>(const TuckPlan&, int, int, int, int, const void*, void*, hipStream_t);
 template hipError_t launch_tucker_disagg<Real>(const TuckPlan&, int, int, int, int, const void*, void*, hipStream_t);
 template hipError_t launch_tucker_pass<Real>(const TuckPlan&, int, int, int, int, const void*, void*, const void*,

@@ -1,5 +1,6 @@
 """The rule that picks the row-streaming kernel (host code, no GPU): its LDS counts what the
-kernel declares itself, and sizes beyond an int are not taken for small ones."""
+kernel declares itself, sizes beyond an int are not taken for small ones, and several right-hand
+sides share a read of the factors wherever a workgroup size allows it and units are enough."""
 import ctypes
 
 import pytest
@@ -19,13 +20,19 @@ class StreamFit(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int32) for n in ("threads", "jmax", "rb", "staged")] + [("lds", ctypes.c_size_t)]
 
 
-def fits(prec, mx, threads, nrhs, dis=True):
-    name = "_ZN7tuckfmm11stream_fitsI%sEEbRKNS_7TuckMaxEiibPNS_9StreamFitE" % ("d" if prec == "c128" else "f")
+def fits(prec, mx, threads, nrhs, dis=True, units=1000):
+    name = "_ZN7tuckfmm11stream_fitsI%sEEbRKNS_7TuckMaxEiiibPNS_9StreamFitE" % ("d" if prec == "c128" else "f")
     fn = getattr(ctypes.CDLL(T.binding.LIB_PATH), name)
     fn.restype = ctypes.c_bool
-    fn.argtypes = [ctypes.POINTER(TuckMax), ctypes.c_int, ctypes.c_int, ctypes.c_bool, ctypes.POINTER(StreamFit)]
+    fn.argtypes = [ctypes.POINTER(TuckMax), ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_bool, ctypes.POINTER(StreamFit)]
     out = StreamFit()
-    return out if fn(ctypes.byref(mx), threads, nrhs, dis, ctypes.byref(out)) else None
+    return out if fn(ctypes.byref(mx), units, threads, nrhs, dis, ctypes.byref(out)) else None
+
+
+def multi_threads(mx, units, threads, nrhs):
+    fn = ctypes.CDLL(T.binding.LIB_PATH)._ZN7tuckfmm13multi_threadsERKNS_7TuckMaxEiii
+    fn.argtypes = [ctypes.POINTER(TuckMax), ctypes.c_int, ctypes.c_int, ctypes.c_int]
+    return fn(ctypes.byref(mx), units, threads, nrhs)
 
 
 def layout(prec, nb, rt, rp, rb, nt, npn, stage=1):
@@ -63,3 +70,27 @@ def test_staging_of_huge_grids(prec, dis):
     mx = layout(prec, 1000, 641, 1, 9, 6700417, 1)
     f = fits(prec, mx, 256, 1, dis)
     assert f is not None and not f.staged
+
+
+# largest items of boxes of 0.5, 1, 1.5, 2 and 4 wavelengths: n_beta, ranks, grid
+BOXES = {0.5: (114, 15, 17, 66, 17, 33), 1.0: (457, 19, 24, 131, 25, 49), 1.5: (1010, 24, 27, 186, 32, 63),
+         2.0: (1791, 25, 30, 235, 38, 75), 4.0: (8684, 39, 54, 381, 64, 127)}
+
+
+@pytest.mark.parametrize("prec", ["c64", "c128"])
+@pytest.mark.parametrize("box", sorted(BOXES))
+@pytest.mark.parametrize("nrhs", [2, 3, 4, 5, 7])
+def test_right_hand_sides_share_a_read(prec, box, nrhs):
+    mx = layout(prec, *BOXES[box])
+    f1 = fits(prec, mx, 256, 1)
+    if f1 is None:  # the general kernel's
+        assert (box, prec) == (4.0, "c128")
+        return
+    t = multi_threads(mx, 2000, 256, nrhs)
+    f = fits(prec, mx, t, nrhs, units=2000)
+    widest = -(-mx.slices // 8)  # slices a wavefront with 512 threads
+    assert (f.rb >= 2) == (widest <= 4) and f.threads >= t
+    if f.rb == 1:
+        assert t == 256
+    # few units: an entry per right-hand side
+    assert fits(prec, mx, multi_threads(mx, 16, 256, nrhs), nrhs, units=16).rb == 1
