@@ -71,9 +71,11 @@ typedef enum {
  * 128, 256 or 512 threads by the mean item size, the longest row and nrhs, or as tuned (the
  * environment variable TUCKFMM_STREAM_THREADS, read at upload, fixes the
  * default; rows too long for the size chosen take more).  Untuned, FMM_C128 and FMM_C64 run
- * them for an odd nrhs and for 2 and 4, and the matrix-core products (FP64 and FP32 MFMA)
- * for an even nrhs from 6; fmm_tucker_tune may choose differently for an nrhs (it offers
- * both paths at any nrhs for these two precisions).  FMM_C128 takes the matrix cores at
+ * them for an odd nrhs, for 2 where two share a read, for 4 where the items are small too,
+ * and for both in layouts of fewer than 128 (group, polarisation) items; for any other even
+ * nrhs they run the matrix-core products (FP64 and FP32 MFMA).  fmm_tucker_tune may choose
+ * differently for an nrhs (it offers both paths at any nrhs for these two precisions).
+ * FMM_C128 takes the matrix cores at
  * every nrhs when the layout's largest item does not fit the FP64 general streaming
  * kernels' LDS (they keep an item's x_g or core-stage vector and its r_beta or angular
  * intermediate there: about 10,000 complex128 values on 160 KB).  The

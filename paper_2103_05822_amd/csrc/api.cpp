@@ -78,12 +78,6 @@ int pack_elems(fmm_prec p) { return p == FMM_C128 ? 1 : 2; }
 bool prec_valid(int p) { return p >= FMM_C128 && p <= FMM_BF16X3; }
 bool prec_is_split(fmm_prec p) { return p == FMM_BF16X2 || p == FMM_BF16X3; }
 
-// Smallest even nrhs for which FMM_C64 and FMM_C128 take the matrix-core products when
-// untuned.  The streaming kernels read the factors once for both stages and up to four
-// right-hand sides: with two they take 137 to 253 us where the matrix cores take 281 to 426
-// (boxes of 0.5 to 2 lambda, 100 to 1000 groups, both precisions); with four the two are
-// within 30% of each other, with more the matrix cores win.
-constexpr int kMfmaMinRhs = 6;
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 bool aligned(const void* p, size_t a) { return reinterpret_cast<uintptr_t>(p) % a == 0; }
@@ -317,6 +311,25 @@ struct Route {
 // precisions are defined for an even nrhs.
 bool mfma_allows(fmm_prec prec, int nrhs) { return !prec_is_split(prec) || nrhs % 2 == 0; }
 
+// Whether an untuned call with an even nrhs streams; the matrix cores read the factors once a
+// stage for all right-hand sides, and win from 6 on.  us, a pass and the two stages, streaming
+// against matrix cores:
+//   2, which share a read: 1 wavelength, 1000 groups, complex64 269 and 421, 693 and 699; 1.5
+//      wavelengths, 160 groups, complex128 256 and 460, 399 and 437; rows too long to share (2
+//      wavelengths, 100 groups, complex128) 287 and 619, 442 and 485.
+//   4, small items (0.5 wavelengths, 1000 groups): complex64 210 and 270, 284 and 307,
+//      complex128 361 and 511, 454 and 475; larger ones (2 wavelengths, 256 groups, complex64)
+//      626 and 1065, 787 and 811; (1 wavelength, 300 groups, complex128) 408 and 639, 417 and 454.
+//   Layouts of few items leave the matrix cores' four launches to a few tiles: 20 groups of 2
+//      wavelengths, complex128, 2 of them 127 and 200, 224 and 273, 4 of them 182 and 322, 233 and
+//      302; 8 groups of 240 functions, complex64, 34 and 52, 52 and 71.
+constexpr double kSmallItem = 3e4;  // mean elements
+bool streams_even(const PrecSlot& s, int nrhs) {
+  if (!s.streams || nrhs > 4) return false;
+  if ((int)s.items.size() < kSplitBelow) return true;
+  return s.shares && (nrhs == 2 || s.mean_unit < kSmallItem);
+}
+
 fmm_status route_of(const PrecSlot& s, fmm_prec prec, int nrhs, Route* r) {
   *r = Route{};
   r->threads = nrhs == 1 || s.fixed_threads ? s.threads : multi_threads(s.plan.mx, s.plan.n_units, s.threads, nrhs);
@@ -327,7 +340,7 @@ fmm_status route_of(const PrecSlot& s, fmm_prec prec, int nrhs, Route* r) {
     r->mfma = true;
     r->variant = prec == FMM_BF16X2 ? 1 : 2;
   } else {
-    r->mfma = nrhs % 2 == 0 && (nrhs >= kMfmaMinRhs || !s.streams);
+    r->mfma = nrhs % 2 == 0 && !streams_even(s, nrhs);
     r->variant = prec == FMM_C128 ? 3 : 0;
   }
   for (const TuneChoice& t : s.tuned)
@@ -676,6 +689,10 @@ extern "C" fmm_status fmm_tucker_upload(fmm_tucker_t h, fmm_prec prec, void* are
     const bool fits = prec == FMM_C128 ? stream_fits<double>(P.mx, n_units, t_staged, 1, true, &f)
                                        : stream_fits<float>(P.mx, n_units, t_staged, 1, true, &f);
     sl.threads = fits && f.staged ? t_staged : t_plain;
+    sl.mean_unit = c;
+    StreamFit f2{};  // as in a layout of enough units
+    sl.shares = (prec == FMM_C128 ? stream_fits<double>(P.mx, 1 << 20, 512, 2, true, &f2)
+                                  : stream_fits<float>(P.mx, 1 << 20, 512, 2, true, &f2)) && f2.rb >= 2;
     sl.fixed_threads = false;
     if (const char* env = std::getenv("TUCKFMM_STREAM_THREADS")) {
       const int v = std::atoi(env);

@@ -91,6 +91,8 @@ struct PrecSlot {
   int threads = 512;                // workgroup size of the streaming kernels for one right-hand side
   bool fixed_threads = false;       // the same for several (else see multi_threads)
   bool streams = true;              // the streaming kernels' LDS fits the largest item
+  bool shares = false;              // two right-hand sides may share a read of the longest row
+  double mean_unit = 0.0;           // streamed elements of a work unit
   std::list<MrhsPlan> mrhs;         // built on first use per (nrhs, knobs); stable addresses
   std::vector<TuneChoice> tuned;
   void* part = nullptr;             // library-owned partial sums of split items (device)

@@ -1,0 +1,69 @@
+"""Which path an untuned call with 2, 4 or 6 right-hand sides takes, told by its bits: layouts of
+few items and, with 2, rows that two right-hand sides may share stream; 4 stream where the items
+are small as well; everything else runs on the matrix cores.  Both paths against the oracle
+(1e-11 in FP64, 1e-5 in FP32), the matrix cores forced, so that they are covered at 2 and 4 too.
+"""
+import numpy as np
+import pytest
+
+import synth
+from oracle import products as pr
+from gpu_util import dev, host, arena, l2_rel, banner
+
+pytestmark = pytest.mark.gpu
+
+T = pytest.importorskip("paper_2103_05822_amd")
+
+TOL = {T.FMM_C128: 1e-11, T.FMM_C64: 1e-5}
+CDT = {T.FMM_C128: np.complex128, T.FMM_C64: np.complex64}
+# name: group sizes, r_beta, and whether 2 and 4 right-hand sides stream
+LAYOUTS = {
+    "few": ([700] * 10, 60, True, True),
+    "small": ([30 + i % 40 for i in range(70)], 20, True, True),
+    "large": ([700] * 70, 60, True, False),
+    "long": ([30] * 69 + [4300], 20, False, False),  # beyond 32 slices in both precisions
+}
+
+
+@pytest.mark.parametrize("prec", [T.FMM_C128, T.FMM_C64], ids=["c128", "c64"])
+@pytest.mark.parametrize("name", list(LAYOUTS))
+def test_route(prec, name):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    sizes, rb, two, four = LAYOUTS[name]
+    lay = T.Layout(7, 11, np.concatenate([[0], np.cumsum(sizes)]))
+    rng = synth.rng(len(sizes))
+    tuck = []
+    for nb in sizes:
+        pair = []
+        for _ in range(2):
+            core, ut, up, ub = synth.synthetic_tucker(rng, 7, 11, nb, 6, 10, min(nb, rb))
+            pair.append((core, (ut, up, ub)))
+        tuck.append(pair)
+    h = T.fmm_tucker_create(lay)
+    try:
+        for g, pair in enumerate(tuck):
+            for a, (core, (ut, up, ub)) in enumerate(pair):
+                T.fmm_tucker_set_group(h, g, a, core, ut, up, ub)
+        ar = arena(T.fmm_tucker_storage_bytes(h, prec)[1])
+        for nrhs, streams in ((2, two), (4, four), (6, False)):
+            banner("route prec=%d layout=%s nrhs=%d" % (prec, name, nrhs))
+            T.fmm_tucker_upload(h, prec, ar)  # forgets the forced choice
+            x = synth.complex_normal(rng, (lay.n_basis, nrhs))
+            gin = synth.complex_normal(rng, (lay.n_groups, 2, lay.n_dir, nrhs))
+            xd, gd = dev(x, CDT[prec]), dev(gin, CDT[prec])
+            f_ref = pr.aggregate_all("tucker", tuck, lay.offsets, x)
+            v_ref = pr.disaggregate_all("tucker", tuck, lay.offsets, gin)
+            got = []
+            for forced in (False, True):
+                if forced:
+                    T.fmm_tucker_set_tuned(h, prec, nrhs, path=1, tile_steps=16, rhs_chunk=nrhs, order=1)
+                F, V = torch.zeros_like(gd), torch.zeros_like(xd)
+                T.fmm_tucker_pass(h, prec, nrhs, xd, F, gd, V)
+                got.append((host(F).copy(), host(V).copy()))
+                assert l2_rel(got[-1][0], f_ref) < TOL[prec] and l2_rel(got[-1][1], v_ref) < TOL[prec]
+            same = all(np.array_equal(a, b) for a, b in zip(*got))
+            assert same == (not streams)
+    finally:
+        T.fmm_tucker_destroy(h)
