@@ -1350,15 +1350,15 @@ size_t tucker_lds_bytes(const TuckMax& mx) {
   return Lds<T>(mx).bytes();
 }
 
-// Whether work entries of two right-hand sides each, in workgroups of `threads`, still hold a
+// Whether work entries of rb right-hand sides each, in workgroups of `threads`, still hold a
 // workgroup of 512 threads per CU.  Below that (layouts of few units) sharing a read of the
 // factors leaves CUs idle, and every right-hand side is an entry of its own: 100 groups of 2
 // wavelengths, complex64, 2 right-hand sides, a pass and the two stages, 169 and 368 us, shared
 // 237 and 415; 8 groups of 240 basis functions 33 and 50, shared 48 and 53; with 3 of them the
 // 100 groups have enough entries: 205 and 475, shared 241 and 427.
 constexpr int64_t kFillThreads = 256 * 512;
-static bool entries_fill(int n_units, int nrhs, int threads) {
-  return (int64_t)n_units * ((nrhs + 1) / 2) * threads >= kFillThreads;
+static bool entries_fill(int n_units, int nrhs, int rb, int threads) {
+  return (int64_t)n_units * ((nrhs + rb - 1) / rb) * threads >= kFillThreads;
 }
 
 static int slices_per_wave(const TuckMax& mx, int threads) { return (mx.slices + threads / 64 - 1) / (threads / 64); }
@@ -1370,10 +1370,10 @@ static int slices_per_wave(const TuckMax& mx, int threads) { return (mx.slices +
 // threads, 12 (more spill).  Two right-hand sides share a read of the factors where the row
 // allows 4 slices and the entries fill the chip.  Four lose to two (1.5 wavelengths, 160
 // groups, complex64, 5 right-hand sides, a pass and the stages: 289 and 534 us with two, 397 and
-// 543 with four), but for 3 or a multiple of 4 where 512 threads hold at most 3 slices and two
-// entries a CU are left (3 right-hand sides: 1 wavelength, 300 groups, complex128, 394 and 667
-// with two, 371 and 609 with four; 2 wavelengths, complex64, 256 groups 596 and 1040, 558 and
-// 991; 100 groups 241 and 427, 394 and 700).  The angular operands are staged in LDS while a CU
+// 543 with four), but for 3 or a multiple of 4 where at least 256 threads hold at most 3 slices
+// and twice the entries are left (3 right-hand sides: 1 wavelength, 300 groups, complex128, 394
+// and 667 with two, 371 and 609 with four; 2 wavelengths, complex64, 256 groups 596 and 1040,
+// 558 and 991; 100 groups 241 and 427, 394 and 700).  The angular operands are staged in LDS while a CU
 // still holds kStageMinWaves wavefronts.
 //
 // Small complex64 items are bound by the latency of each unit's phases, which more workgroups
@@ -1388,8 +1388,8 @@ bool stream_fits(const TuckMax& mx, int n_units, int threads, int nrhs, bool dis
     const int jmax = small ? 2 : (j <= 4 ? 4 : (j <= 8 ? 8 : (j <= 12 && threads == 512 ? 12 : 0)));
     if (!jmax) continue;
     int most = 1;
-    if (jmax == 4 && nrhs > 1 && entries_fill(n_units, nrhs, threads))
-      most = threads == 512 && j <= 3 && (nrhs + 1) % 4 < 2 && (int64_t)n_units * ((nrhs + 3) / 4) >= 512 ? 4 : 2;
+    if (jmax == 4 && nrhs > 1 && entries_fill(n_units, nrhs, 2, threads))
+      most = threads >= 256 && j <= 3 && (nrhs + 1) % 4 < 2 && entries_fill(n_units, nrhs, 4, threads / 2) ? 4 : 2;
     for (int rb = most; rb >= 1; rb /= 2) {
       const size_t staged = StreamLds<T>(mx, nw, rb, true, dis).bytes();
       const size_t plain = StreamLds<T>(mx, nw, rb, false, dis).bytes();
@@ -1420,7 +1420,7 @@ int multi_threads(const TuckMax& mx, int n_units, int threads, int nrhs) {
   while (t < 512 && slices_per_wave(mx, t) > most) t *= 2;
   if (slices_per_wave(mx, t) > 4) return threads;
   for (; t <= 512; t *= 2) {
-    if (entries_fill(n_units, nrhs, t)) return t;
+    if (entries_fill(n_units, nrhs, 2, t)) return t;
     if (t >= threads) break;
   }
   return threads;
@@ -1462,6 +1462,7 @@ hipError_t launch_stream(StreamArgs<T> a, const StreamFit& f, hipStream_t s) {
   TFMM_STREAM_CASE(128, 8, 1)
   TFMM_STREAM_CASE(256, 4, 1)
   TFMM_STREAM_CASE(256, 4, 2)
+  TFMM_STREAM_CASE(256, 4, 4)
   TFMM_STREAM_CASE(256, 8, 1)
   TFMM_STREAM_CASE(512, 4, 1)
   TFMM_STREAM_CASE(512, 4, 2)
