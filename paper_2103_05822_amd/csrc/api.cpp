@@ -312,22 +312,23 @@ struct Route {
 bool mfma_allows(fmm_prec prec, int nrhs) { return !prec_is_split(prec) || nrhs % 2 == 0; }
 
 // Whether an untuned call with an even nrhs streams; the matrix cores read the factors once a
-// stage for all right-hand sides, and win from 6 on.  us, a pass and the two stages, streaming
-// against matrix cores:
-//   2, which share a read: 1 wavelength, 1000 groups, complex64 269 and 421, 693 and 699; 1.5
-//      wavelengths, 160 groups, complex128 256 and 460, 399 and 437; rows too long to share (2
-//      wavelengths, 100 groups, complex128) 287 and 619, 442 and 485.
-//   4, small items (0.5 wavelengths, 1000 groups): complex64 210 and 270, 284 and 307,
-//      complex128 361 and 511, 454 and 475; larger ones (2 wavelengths, 256 groups, complex64)
-//      626 and 1065, 787 and 811; (1 wavelength, 300 groups, complex128) 408 and 639, 417 and 454.
+// stage for all right-hand sides, and win from 6 on.  A pass equals its stages bit for bit, so
+// both take one path: streaming where it gains in a pass and loses at most a few per cent in the
+// stages.  us, a pass and the two stages, streaming against matrix cores:
+//   2, which share a read: 1 wavelength, 1000 groups, complex64 299 and 446, 693 and 699; 1.5
+//      wavelengths, 160 groups, complex128 273 and 461, 399 and 437; rows too long to share (2
+//      wavelengths, 100 groups, complex128) 287 and 619, 447 and 485.
+//   4, small items: 0.5 wavelengths, 1000 groups, complex128 361 and 511, 454 and 475; 1
+//      wavelength, 300 groups, complex64 196 and 302, 276 and 295, complex128 408 and 639, 417
+//      and 454; 1.5 wavelengths, 160 groups, complex64 212 and 377, 301 and 339; 2 wavelengths,
+//      256 groups, complex64 626 and 1065, 787 and 811.
 //   Layouts of few items leave the matrix cores' four launches to a few tiles: 20 groups of 2
 //      wavelengths, complex128, 2 of them 127 and 200, 224 and 273, 4 of them 182 and 322, 233 and
 //      302; 8 groups of 240 functions, complex64, 34 and 52, 52 and 71.
-constexpr double kSmallItem = 3e4;  // mean elements
-bool streams_even(const PrecSlot& s, int nrhs) {
+bool streams_even(const PrecSlot& s, fmm_prec prec, int nrhs) {
   if (!s.streams || nrhs > 4) return false;
   if ((int)s.items.size() < kSplitBelow) return true;
-  return s.shares && (nrhs == 2 || s.mean_unit < kSmallItem);
+  return s.shares && (nrhs == 2 || s.mean_unit < (prec == FMM_C128 ? 3e4 : 2e5));
 }
 
 fmm_status route_of(const PrecSlot& s, fmm_prec prec, int nrhs, Route* r) {
@@ -340,7 +341,7 @@ fmm_status route_of(const PrecSlot& s, fmm_prec prec, int nrhs, Route* r) {
     r->mfma = true;
     r->variant = prec == FMM_BF16X2 ? 1 : 2;
   } else {
-    r->mfma = nrhs % 2 == 0 && !streams_even(s, nrhs);
+    r->mfma = nrhs % 2 == 0 && !streams_even(s, prec, nrhs);
     r->variant = prec == FMM_C128 ? 3 : 0;
   }
   for (const TuneChoice& t : s.tuned)

@@ -20,7 +20,7 @@ CDT = {T.FMM_C128: np.complex128, T.FMM_C64: np.complex64}
 LAYOUTS = {
     "few": ([700] * 10, 60, True, True),
     "small": ([30 + i % 40 for i in range(70)], 20, True, True),
-    "large": ([700] * 70, 60, True, False),
+    "large": ([1900] * 70, 120, True, False),
     "long": ([30] * 69 + [4300], 20, False, False),  # beyond 32 slices in both precisions
 }
 
