@@ -66,7 +66,7 @@ struct MrhsPlan {
   int nrhs = 0;
   int rhs_chunk = 0;   // columns per chunk
   int tile_steps = 0;  // K steps a workgroup aims to run (column blocks per tile)
-  int order = 0;       // angular contraction order: 0 each item's cheaper, 1 theta first, 2 phi first, 3 untuned
+  int order = 0;       // angular contraction order: 0 each item's cheaper, 1 theta first, 2 phi first
   char* dev = nullptr;  // one allocation: problem tables, tile lists, scratch
   size_t dev_bytes = 0;
   char* scratch = nullptr;
@@ -106,7 +106,7 @@ constexpr int kMrhsDefaultSteps = 16;
 constexpr int kMrhsFewSteps = 8;     // the same for layouts of at most kMrhsFewItems items
 constexpr size_t kMrhsFewItems = 64;
 constexpr int kMrhsDefaultChunk = 64;
-constexpr int kMrhsUntunedOrder = 3;  // angular order of untuned calls (see mrhs_build_host)
+constexpr int kMrhsUntunedOrder = -1;  // angular order left to the plan (see mrhs_get)
 // Host image of the tables: problems [8][n_items] (product j of item i at j n_items + i)
 // and tile lists [agg, dis, pass][launch] per chunk; scratch offsets in complex elements.
 struct MrhsHostChunk {
@@ -120,7 +120,7 @@ struct MrhsHost {
 };
 void mrhs_build_host(const std::vector<TuckItem>& items, const Layout& L, int nrhs, int tile_steps, int rhs_chunk,
                      int order, MrhsHost* out);
-// Plan for (slot, nrhs) with the given knobs (0 = defaults), built on first use.
+// Plan for (slot, nrhs) with the given knobs (0, order -1 = defaults), built on first use.
 // elem_bytes: 8 (complex64 slot) or 16 (complex128 slot), the size of a scratch value.
 fmm_status mrhs_get(PrecSlot& s, size_t elem_bytes, const Layout& L, int nrhs, int tile_steps, int rhs_chunk,
                     int order, MrhsPlan** out);

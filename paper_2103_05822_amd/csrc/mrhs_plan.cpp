@@ -213,18 +213,12 @@ void mrhs_release(PrecSlot& s) {
 
 void mrhs_build_host(const std::vector<TuckItem>& items_in, const Layout& L, int nrhs, int tile_steps,
                      int rhs_chunk, int order, MrhsHost* out) {
-  // the angular order: each item's cheaper one (order 0), theta (1) or phi (2) first for
-  // every item, or the untuned rule: theta first unless phi first saves a quarter of the
-  // multiply-adds.  Theta first contracts phi, the longer index, over G's contiguous
-  // directions; at equal work it took 2-7% less time (us, theta first against each item's
-  // cheaper order: 1360 and 1409, 682 and 723, 760 and 793 on 100-300 groups).
+  // the angular order: each item's cheaper one (order 0), or theta (1) / phi (2) first
+  // for every item
   std::vector<TuckItem> items(items_in);
-  for (TuckItem& it : items) {
-    if (it.ident || order == 0) continue;
-    const double c_theta = (double)L.n_theta * it.rp * (it.rt + L.n_phi);
-    const double c_phi = (double)it.rt * L.n_phi * (it.rp + L.n_theta);
-    it.theta_first = order == 1 || (order == kMrhsUntunedOrder && c_phi > 0.75 * c_theta) ? 1 : 0;
-  }
+  if (order == 1 || order == 2)
+    for (TuckItem& it : items)
+      if (!it.ident) it.theta_first = order == 1 ? 1 : 0;
   const int n_items = (int)items.size();
   const int n_chunks = (nrhs + rhs_chunk - 1) / rhs_chunk;
   // scratch: per item, three blocks per stage (sized for a full chunk)
@@ -274,6 +268,27 @@ void mrhs_build_host(const std::vector<TuckItem>& items_in, const Layout& L, int
   }
 }
 
+namespace {
+
+// The angular order of untuned calls, one of those the tuner offers, so that a tuned call loses
+// nothing: theta first for all, unless each item's cheaper order saves a quarter of the
+// multiply-adds.  Theta first contracts phi, the longer index, over G's contiguous directions;
+// at equal work it took 2-7% less time (us, theta first against each item's cheaper order: 1360
+// and 1409, 682 and 723, 760 and 793 on 100-300 groups).
+int untuned_order(const std::vector<TuckItem>& items, const Layout& L) {
+  double theta = 0.0, cheaper = 0.0;
+  for (const TuckItem& it : items) {
+    if (it.ident) continue;
+    const double c_theta = (double)L.n_theta * it.rp * (it.rt + L.n_phi);
+    const double c_phi = (double)it.rt * L.n_phi * (it.rp + L.n_theta);
+    theta += c_theta;
+    cheaper += std::min(c_theta, c_phi);
+  }
+  return cheaper > 0.75 * theta ? 1 : 0;
+}
+
+}  // namespace
+
 fmm_status mrhs_get(PrecSlot& s, size_t elem_bytes, const Layout& L, int nrhs, int tile_steps, int rhs_chunk,
                     int order, MrhsPlan** out) {
   // few items leave most of the chip to the angular products' tiles: shorter ones then (16
@@ -283,7 +298,7 @@ fmm_status mrhs_get(PrecSlot& s, size_t elem_bytes, const Layout& L, int nrhs, i
   // (any nrhs: the paired 16-byte loads read factor rows only; the callers keep the
   // bf16 split precisions to an even nrhs)
   rhs_chunk = std::min(rhs_chunk, nrhs);
-  if (order < 0 || order > kMrhsUntunedOrder) order = 0;
+  if (order < 0 || order > 2) order = untuned_order(s.items, L);
   for (auto& p : s.mrhs)
     if (p.nrhs == nrhs && p.tile_steps == tile_steps && p.rhs_chunk == rhs_chunk && p.order == order) {
       *out = &p;
