@@ -356,6 +356,9 @@ def main():
                      "unit": "GB/s", "frac": round(roof_bytes / (ms[dom] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                      "traffic": measured_traffic("tucker_pass_kernel<float>", "tucker.hip", w.name),
                      "bytes_per_launch": roof_bytes},
+        "GBps_counts": "value and every Tucker *GBps field count the factors once per stage, the work of the two "
+                       "calls that a pass replaces, so they may exceed the peak; roofline and hbm_frac count "
+                       "each factor byte once per pass, as it is read",
         "copy_GBps": round(copy_gbs, 1),
         "memory_MB": {"tucker_factors_f32": round(fac32 / 2 ** 20, 1),
                       "dense_f64": round(2 * N * nd * 16 / 2 ** 20, 1)},
@@ -808,7 +811,7 @@ def svd_comparison(args, T, torch, lay, dense, w, x32, g32, tucker_ms, tucker_fa
         ms = float(np.mean([a.elapsed_time(b) for a, b in evs]))
         b_stage, fac = svd_stage_bytes(rs, lay.offsets, w.n_theta, w.n_phi, 8)
         assert fac == fbytes, (fac, fbytes)
-        gbs = 2 * b_stage / (ms * 1e-3) / 1e9  # factors once per stage; hbm_frac: once
+        gbs = 2 * b_stage / (ms * 1e-3) / 1e9  # factors once per stage
         rep = {"compress_s": round(t_c, 2), "r_beta_mean": round(float(rs[..., 2].mean()), 2),
                "factors_MB_f32": round(fbytes / 2 ** 20, 1),
                "tucker_factors_MB_f32": round(tucker_fac_bytes / 2 ** 20, 1),

@@ -2,8 +2,8 @@
 // to a few right-hand sides.
 //
 // One workgroup of NT = 64, 128, 256 or 512 threads per (group, polarisation) work item and
-// block of right-hand sides, NT chosen from the mean item size.  Work lists are sorted by
-// decreasing cost (longest-processing-time order).  In layouts of few items, large items
+// block of right-hand sides, NT chosen from the mean item size and, for several right-hand
+// sides, the longest row.  Work lists are sorted by decreasing cost (longest-processing-time order).  In layouts of few items, large items
 // run as blocks of their r_beta rows (work units) whose partial sums a finishing kernel adds
 // in block order.  Per item (g, alpha), the angular order chosen on the host:
 //   S[a,c] = sum U^theta[i][a] U^phi[j][c] conj(G[i,j])    angular phase, matrix cores
@@ -662,7 +662,7 @@ __global__ __launch_bounds__(kGenThreads) void tucker_general_kernel(
 // uniform scalars for the axpy.
 //
 // The sweep is bound by HBM.  A stage alone runs the same code with the other stage's
-// vector zero, so a pass equals its two stages bit for bit.
+// vector zero (or its products left out), so a pass equals its two stages bit for bit.
 
 // Sum of v and its partner lane across lane bit BIT (BIT = 4 pairs lanes i and 7 - i of
 // eight, which later steps over bits 2 and 1 complete to the same sums).
