@@ -3,9 +3,10 @@
 //
 // One workgroup of NT = 64, 128, 256 or 512 threads per (group, polarisation) work item and
 // block of right-hand sides, NT chosen from the mean item size and, for several right-hand
-// sides, the longest row.  Work lists are sorted by decreasing cost (longest-processing-time order).  In layouts of few items, large items
-// run as blocks of their r_beta rows (work units) whose partial sums a finishing kernel adds
-// in block order.  Per item (g, alpha), the angular order chosen on the host:
+// sides, the longest row.  Work lists are sorted by decreasing cost
+// (longest-processing-time order).  In layouts of few items, large items run as blocks of
+// their r_beta rows (work units) whose partial sums a finishing kernel adds in block order.
+// Per item (g, alpha), the angular order chosen on the host:
 //   S[a,c] = sum U^theta[i][a] U^phi[j][c] conj(G[i,j])    angular phase, matrix cores
 //   for every row b of U^beta^T and the core:
 //     y[b] = sum_n U^beta[n][b] x[n],   t[q] += core[b][q] y[b]
@@ -1011,6 +1012,7 @@ struct StreamArgs {
   const TuckWork* work;
   const TuckSplit* splits;
   int n_units, n_theta, n_phi, nrhs, rstep, n_rblk;
+  int blk_x;  // a stage's grid: blocks of a unit along x (1 or n_rblk; else along y)
   TuckMax mx;
   int staged;
   const typename Tr<T>::c* x;  // nullptr: no aggregation
@@ -1196,9 +1198,8 @@ void tucker_pass_kernel(StreamArgs<T> a) {
   const int total = a.n_units * a.n_rblk;
   if (a.next == nullptr) {
     int32_t none;
-    const int iu = gridDim.y == 1 ? blockIdx.x / a.n_rblk : blockIdx.x;
-    const int blk = gridDim.y == 1 ? blockIdx.x - iu * a.n_rblk : blockIdx.y;
-    stream_entry<T, NT, JMAX, RB>(a, L, smem, iu, blk, none);
+    const int iu = blockIdx.x / a.blk_x;
+    stream_entry<T, NT, JMAX, RB>(a, L, smem, iu, blockIdx.y + blockIdx.x - iu * a.blk_x, none);
     return;
   }
   int32_t mine = 0;  // (first thread) the next entry, taken when the current one's sweep is done
@@ -1428,12 +1429,13 @@ int multi_threads(const TuckMax& mx, int n_units, int threads, int nrhs) {
 #endif
 
 template <typename T, int NT, int JMAX, int RB>
-hipError_t launch_stream_kernel(const StreamArgs<T>& a, const StreamFit& f, int64_t entries, hipStream_t s) {
+hipError_t launch_stream_kernel(StreamArgs<T> a, const StreamFit& f, int64_t entries, hipStream_t s) {
   // A stage: the column blocks of a unit follow each other (see stream_entry; 140 items of mean
   // 1.7M elements, complex64, the two stages with 3 right-hand sides: 2420 us in the other order,
   // now 2180).  Split items go by columns first: their units are alike, and 20 groups of 2
   // wavelengths took 5% less so.
   const bool flat = a.splits == nullptr && entries <= (1 << 22);
+  a.blk_x = flat ? a.n_rblk : 1;
   dim3 grid((unsigned)(flat ? entries : a.n_units), (unsigned)(flat ? 1 : a.n_rblk));
   if (a.next) {
     const hipError_t e = persistent_grid(&tucker_pass_kernel<T, NT, JMAX, RB>, NT, f.lds, entries, &grid.x);
