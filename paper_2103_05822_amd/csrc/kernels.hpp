@@ -17,7 +17,7 @@ hipError_t launch_tucker_disagg(const TuckPlan& pl, int threads, int n_theta, in
 template <typename T>
 hipError_t launch_tucker_pass(const TuckPlan& pl, int threads, int n_theta, int n_phi, int nrhs, const void* x,
                               void* F, const void* G, void* V, hipStream_t s);
-// LDS of the general Tucker kernels, which bounds the layouts that the streaming path
+// LDS of the general Tucker kernel, which bounds the layouts that the streaming path
 // takes.
 template <typename T>
 size_t tucker_lds_bytes(const TuckMax& mx);

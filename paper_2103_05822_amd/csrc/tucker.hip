@@ -21,8 +21,8 @@
 //
 // One-right-hand-side pass on an MI355X, before (one read of the factors per stage, angular
 // products on the vector units) and now: 4000 items of mean 15k elements, complex64, 231 and
-// 126 us (510 MB: 4.0 TB/s); 512 items of mean 259k 398 and 230 us (1.2 GB: 5.2 TB/s); both
-// stages alone, complex128, 800 items of mean 58k 472 and 310 us (1.6 GB: 5.2 TB/s).
+// 128 us (510 MB: 4.0 TB/s); 512 items of mean 259k 398 and 229 us (1.2 GB: 5.2 TB/s); both
+// stages alone, complex128, 800 items of mean 58k 472 and 307 us (1.6 GB: 5.2 TB/s).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
